@@ -293,7 +293,7 @@ struct Image {
   size_t put_vec(const std::vector<T>& v) { return put(v.data(), v.size() * sizeof(T)); }
 };
 
-enum Kind { K_GENERIC = 1, K_GEMM, K_GEMM32, K_RMSNORM, K_SOFTMAX, K_ATTENTION, K_REPART };
+enum Kind { K_GENERIC = 1, K_GEMM, K_CONTRACT, K_RMSNORM, K_SOFTMAX, K_ATTENTION, K_REPART };
 
 // row-reduction plan constants (see RowArgs)
 struct RowLayout {
@@ -324,6 +324,9 @@ struct Plan {
   bool gemm_direct = false;  // direct-load kernel (work list of GemmUnit), else GemmTile
   int gemm_tn = kGemmTN;     // output tile columns per right operand (256, or 128)
   GemmTupleMeta* d_gemm_meta = nullptr;  // direct-load plans: per-tuple operand blocks
+  // contraction: everything of its arguments but the data pointers
+  ContractArgs con;
+  int con_a = 0;  // input that is the kernel's A
   // repartition: tasks of kRepTaskBytesSmall (relations below kRepLargeBytes)
   bool rep_small = false;
   // rows
@@ -395,6 +398,7 @@ struct OpInfo {
   int gqa = 1;                   // query heads per key/value head (attention)
   char gh = 0, gg = 0;           // query-head and key/value-head letters (gqa > 1)
   int head_dim = -1;             // their dim in Q and in K/V
+  ContractDims con{};            // letters of a two-operand contraction (dims only)
   std::vector<int64_t> seq_ends; // packed sequences along cq/ck (attention), empty: one
 };
 
@@ -482,6 +486,75 @@ int64_t max_block_bytes(const ea_relation* r) {
   return n;
 }
 
+// ts x ts tiles of every output block of a contraction (per batch index)
+constexpr int64_t kConMaxWork = int64_t(1) << 20;
+int64_t contract_tiles(const ea_relation* c, const ContractDims& d, int ts) {
+  int64_t n = 1;
+  for (int dim : {d.cm, d.cn}) {
+    if (dim < 0) continue;
+    int64_t k = 0;
+    for (int b = 0; b < c->nb[dim]; ++b) k += (c->splits[dim][b + 1] - c->splits[dim][b] + ts - 1) / ts;
+    n *= k;
+  }
+  return n;
+}
+
+// A two-operand product that the contraction kernels take: both inputs of one
+// dtype; one letter in both and not in the output; every other letter in
+// exactly one input and the output (at most one per input), or in all three
+// (at most kConMaxBatch).  A is the operand without the output's last letter
+// where there is a choice, so that stores run along memory (a product of two
+// floats does not depend on their order).
+bool contraction_ok(const Spec& sp, const ea_relation* const* ops, ContractDims* d) {
+  if (sp.n_in != 2 || ops[0]->dtype != ops[1]->dtype) return false;
+  for (int o = 0; o < 3; ++o)  // 32-bit byte offsets inside a block
+    if (max_block_bytes(ops[o]) >= INT32_MAX) return false;
+  const char last = sp.let[2][sp.rank[2] - 1];
+  const int a = find_dim(sp, 0, last) >= 0 && find_dim(sp, 1, last) < 0 ? 1 : 0, b = 1 - a;
+  memset(d, 0, sizeof(*d));
+  d->a_op = a;
+  d->a_rank = sp.rank[a];
+  d->b_rank = sp.rank[b];
+  d->c_rank = sp.rank[2];
+  d->am = d->ak = d->bk = d->bn = d->cm = d->cn = -1;
+  int n_batch = 0;
+  for (int x = 0; x < sp.rank[a]; ++x) {
+    const char l = sp.let[a][x];
+    const int y = find_dim(sp, b, l), z = find_dim(sp, 2, l);
+    if (y >= 0 && z >= 0) {
+      if (n_batch == kConMaxBatch) return false;
+      d->ab[n_batch] = x;
+      d->bb[n_batch] = y;
+      d->cb[n_batch] = z;
+      ++n_batch;
+    } else if (y >= 0) {
+      if (d->ak >= 0) return false;
+      d->ak = x;
+      d->bk = y;
+    } else if (z >= 0) {
+      if (d->am >= 0) return false;
+      d->am = x;
+      d->cm = z;
+    } else {
+      return false;
+    }
+  }
+  for (int y = 0; y < sp.rank[b]; ++y) {
+    const char l = sp.let[b][y];
+    if (find_dim(sp, a, l) >= 0) continue;
+    const int z = find_dim(sp, 2, l);
+    if (z < 0 || d->bn >= 0) return false;
+    d->bn = y;
+    d->cn = z;
+  }
+  for (int i = n_batch; i < kConMaxBatch; ++i) d->ab[i] = d->bb[i] = d->cb[i] = -1;
+  if (d->ak < 0) return false;
+  // a bounded work list (one record per tile and batch index)
+  int64_t work = contract_tiles(ops[2], *d, 64);
+  for (int i = 0; i < n_batch && work <= kConMaxWork; ++i) work *= ops[2]->shape[d->cb[i]];
+  return work <= kConMaxWork;
+}
+
 bool is_float_dtype(int32_t dt) { return dt == EA_F32 || dt == EA_BF16 || dt == EA_F16; }
 
 int classify(const Spec& sp, int32_t join_op, int32_t agg_op, const ea_relation* const* ops,
@@ -512,23 +585,6 @@ int classify(const Spec& sp, int32_t join_op, int32_t agg_op, const ea_relation*
           if (r->splits[d] != o->splits[d]) return fail(EA_ERR_ARG, "residual partition differs from the output's");
         if (!r->data) return fail(EA_ERR_ARG, "residual relation has no data");
       }
-      // fp32 block products "ab,bc->ac" / "ab,cb->ac" without a residual:
-      // the vector-ALU tile kernel
-      if (join_op == EA_JOIN_MUL && agg_op == EA_AGG_SUM && n_in == 2 && sp.rank[0] == 2 && sp.rank[1] == 2 &&
-          sp.rank[2] == 2 && ops[0]->dtype == EA_F32 && ops[1]->dtype == EA_F32 && !(prm && prm->residual)) {
-        const char a = sp.let[0][0], b = sp.let[0][1];
-        const char* L1 = sp.let[1];
-        const char* L2 = sp.let[2];
-        int kmaj = -1;
-        char c = 0;
-        if (L1[0] == b && L1[1] != a && L1[1] != b) { kmaj = 0; c = L1[1]; }
-        else if (L1[1] == b && L1[0] != a && L1[0] != b) { kmaj = 1; c = L1[0]; }
-        if (kmaj >= 0 && L2[0] == a && L2[1] == c) {
-          oi->kind = K_GEMM32;
-          oi->b_kmajor = kmaj;
-          return EA_OK;
-        }
-      }
       // matrix-core path: "ab,bc->ac" or "ab,cb->ac", 16-bit inputs, SUM of products
       if (join_op == EA_JOIN_MUL && agg_op == EA_AGG_SUM && n_in == 2 && sp.rank[0] == 2 &&
           sp.rank[1] == 2 && sp.rank[2] == 2 && ops[0]->dtype == ops[1]->dtype &&
@@ -550,9 +606,11 @@ int classify(const Spec& sp, int32_t join_op, int32_t agg_op, const ea_relation*
           if (aligned) {
             oi->kind = K_GEMM;
             oi->b_kmajor = kmaj;
+            return EA_OK;
           }
         }
       }
+      if (join_op == EA_JOIN_MUL && agg_op == EA_AGG_SUM && contraction_ok(sp, ops, &oi->con)) oi->kind = K_CONTRACT;
       return EA_OK;
     }
     case EA_OP_SWIGLU: {
@@ -1044,6 +1102,100 @@ GemmDlPlan gemm_units_dl(const ea_relation* a, const ea_relation* c, int tn, con
   return bal_cost < ev_cost ? bal : ev;
 }
 
+// Output tile of a contraction plan: the cheapest under a time model (us) of
+// the three kernels, fitted to fp32 products on one card (measured | model):
+//                            16 x 16      32 x 32      64 x 64
+//   256 x 256 x 256         3.7 |  3.5   5.8 |  7.0  10.7 | 10.6
+//   512 x 512 x 512         9.7 | 11     8.5 |  9.1  16.1 | 16.2
+//   512 x 2048 x 512       27.1 | 32    23.0 | 21    51.4 | 50
+//   768 x 768 x 768        24.5 | 30    21.0 | 21    23.0 | 22
+//   1024 x 128 x 1024      30.6 | 16    17.6 | 14     7.8 |  7.8
+//   1024 x 1024 x 1024     53.7 | 66    35.1 | 42    30.6 | 27
+//   2048 x 2048 x 2048      503 | 490    301 | 292    150 | 171
+// The small tiles pay per k value of a tile (operand loads) and per tile; they
+// win while the 64 x 64 tiles are too few for the 256 CUs, whose cost is per
+// 32-deep step.  An operand read along k without vectors (block extents not
+// multiples of four) scatters a load of the small tiles over as many cache
+// lines as rows: 3 times the cost (72 tiles of 12 x 101 x 77 x 133: 13.5 us
+// with 32 x 32 tiles against 9.4 us with 64 x 64).
+int contract_tile(const ea_relation* c, const ContractDims& d, int64_t batch, int64_t K, int64_t steps, int scattered) {
+  const double load = 1.0 + scattered;  // operands read along k without vectors: 0, 1 or 2
+  auto share = [&](int ts) { return (double)(contract_tiles(c, d, ts) * batch) / 256.0; };
+  const double c16 = 2.2 + load * std::max(1.0, share(16)) * (0.4 + 3.5e-3 * (double)K);
+  const double c32 = 3.5 + load * std::max(1.0, share(32)) * (1.5 + 8.0e-3 * (double)K);
+  const double s64 = share(64);
+  const double c64 = 5.0 + (double)steps * (s64 <= 1.0 ? 0.7 : 0.65 * std::ceil(s64));
+  if (c64 <= c32 && c64 <= c16) return 64;
+  return c32 <= c16 ? 32 : 16;
+}
+
+int build_contract(const ea_relation* const* ops, const ContractDims& d, int64_t tuple_cap, Image* img, Extra* ex,
+                   ContractArgs* a) {
+  const ea_relation *A = ops[d.a_op], *B = ops[1 - d.a_op], *C = ops[2];
+  memset(a, 0, sizeof(*a));
+  int64_t batch = 1;
+  for (int i = 0; i < kConMaxBatch && d.ab[i] >= 0; ++i) {
+    ++a->n_batch;
+    batch *= C->shape[d.cb[i]];
+  }
+  a->dt_in = A->dtype;
+  a->dt_out = C->dtype;
+  a->nt = A->nb[d.ak];
+  // contiguous letter: the row (column) letter when it is the operand's last,
+  // else the contracted one is read along k; vectors of four when the
+  // contiguous letter's block extents are multiples of four (every other
+  // stride is then one too, and blocks start at 256-byte multiples)
+  auto last_ok = [](const ea_relation* r, int dim) {
+    if (dim != r->rank - 1) return false;
+    for (int64_t v : r->splits[dim])
+      if (v % 4) return false;
+    return true;
+  };
+  a->rmaj_a = d.am == A->rank - 1;
+  a->rmaj_b = d.bn == B->rank - 1;
+  a->vec_a = last_ok(A, A->rank - 1) && (a->rmaj_a || d.ak == A->rank - 1);
+  a->vec_b = last_ok(B, B->rank - 1) && (a->rmaj_b || d.bk == B->rank - 1);
+  const std::vector<int64_t>& ks = A->splits[d.ak];
+  for (int t = 0; t < a->nt; ++t) a->n_steps += (int32_t)((ks[t + 1] - ks[t] + 31) / 32);
+  a->tile = contract_tile(C, d, batch, A->shape[d.ak], a->n_steps, (!a->rmaj_a && !a->vec_a) + (!a->rmaj_b && !a->vec_b));
+  if (a->tile < 64) {
+    const int kg = 256 / a->tile;  // k values per group (four MFMAs)
+    std::vector<int64_t> pre(1, 0);
+    for (int t = 0; t < a->nt; ++t) pre.push_back(pre.back() + (ks[t + 1] - ks[t] + kg - 1) / kg);
+    for (int i = 0; i < kConWaves; ++i) {
+      const int64_t g0 = pre.back() * i / kConWaves, g1 = pre.back() * (i + 1) / kConWaves;
+      const int t = (int)(std::upper_bound(pre.begin(), pre.end(), g0) - pre.begin()) - 1;
+      a->run[i].t = std::min(t, a->nt - 1);
+      a->run[i].g = g1 > g0 ? (int32_t)(g0 - pre[(size_t)t]) : 0;
+      a->run[i].n = (int32_t)(g1 - g0);
+    }
+  }
+  std::vector<ConWork> work;
+  int32_t co[kMaxRank];
+  for (int64_t b = 0; b < C->nblocks; ++b) {
+    block_coords(C, b, co);
+    auto ext = [&](int dim) { return dim < 0 ? 1 : C->splits[dim][co[dim] + 1] - C->splits[dim][co[dim]]; };
+    int64_t nb = 1;
+    for (int i = 0; i < a->n_batch; ++i) nb *= ext(d.cb[i]);
+    const int64_t me = ext(d.cm), ne = ext(d.cn);
+    for (int64_t x = 0; x < nb; ++x)
+      for (int64_t m0 = 0; m0 < me; m0 += a->tile)
+        for (int64_t n0 = 0; n0 < ne; n0 += a->tile) {
+          ConWork w;
+          memset(&w, 0, sizeof(w));
+          w.block = (int32_t)b;
+          w.m0 = (int32_t)m0;
+          w.n0 = (int32_t)n0;
+          w.batch = (int32_t)x;
+          work.push_back(w);
+        }
+  }
+  ex->work = img->put_vec(work);
+  ex->n_work = (int64_t)work.size();
+  ex->meta = img->put_zero((size_t)tuple_cap * sizeof(ConMeta));
+  return EA_OK;
+}
+
 int build_rows(const Spec& sp, const ea_relation* const* ops, const OpInfo& oi, Image* img, Extra* ex,
                RowLayout* lay) {
   // rows of a group: points of the group letters' box; every group has the
@@ -1259,7 +1411,7 @@ int get_joinagg_plan(const char* spec_str, const Spec& sp, int32_t join_op, int3
   for (int64_t e : oi.seq_ends) k << e << ",";
   for (int o = 0; o <= sp.n_in; ++o) key_rel(k, ops[o]);
   const ea_relation* res = prm ? prm->residual : nullptr;
-  if (res && (oi.kind == K_GEMM || oi.kind == K_GENERIC)) k << "|res" << res->dtype;
+  if (res && (oi.kind == K_GEMM || oi.kind == K_GENERIC || oi.kind == K_CONTRACT)) k << "|res" << res->dtype;
   const std::string key = k.str();
   std::lock_guard<std::mutex> lk(g_cache_mu);
   auto it = cache().find(key);
@@ -1331,22 +1483,7 @@ int get_joinagg_plan(const char* spec_str, const Spec& sp, int32_t join_op, int3
       p->ws_partial_bytes = slots * kGemmTM * kGemmTN * (int64_t)sizeof(float);
       break;
     }
-    case K_GEMM32: {  // square tiles of every output block
-      std::vector<Gemm32Work> work;
-      const ea_relation* c = ops[sp.n_in];
-      int32_t co[kMaxRank];
-      for (int64_t b = 0; b < c->nblocks; ++b) {
-        block_coords(c, b, co);
-        const int64_t me = c->splits[0][co[0] + 1] - c->splits[0][co[0]];
-        const int64_t ne = c->splits[1][co[1] + 1] - c->splits[1][co[1]];
-        for (int64_t m0 = 0; m0 < me; m0 += kGemm32Tile)
-          for (int64_t n0 = 0; n0 < ne; n0 += kGemm32Tile)
-            work.push_back(Gemm32Work{(int32_t)b, (int32_t)m0, (int32_t)n0, 0});
-      }
-      ex.work = img.put_vec(work);
-      ex.n_work = (int64_t)work.size();
-      break;
-    }
+    case K_CONTRACT: e = build_contract(ops, oi.con, p->tuple_cap, &img, &ex, &p->con); break;
     case K_RMSNORM:
     case K_SOFTMAX: e = build_rows(sp, ops, oi, &img, &ex, &p->rows); break;
     case K_ATTENTION: break;  // work units follow the GPU join (below)
@@ -1377,6 +1514,21 @@ int get_joinagg_plan(const char* spec_str, const Spec& sp, int32_t join_op, int3
     a.n_units = (int32_t)p->n_work;
     a.meta = p->d_gemm_meta;
     EA_HIP_TRY(launch_gemm_prep(a, (GemmUnit*)(p->dmem + ex.work), p->tuple_cap, s));
+    EA_HIP_TRY(hipStreamSynchronize(s));
+  }
+  if (oi.kind == K_CONTRACT) {  // the join and the block tables resolved into the work list
+    p->con_a = oi.con.a_op;
+    p->con.n_work = p->n_work;
+    p->con.work = (const ConWork*)(p->dmem + ex.work);
+    p->con.meta = (const ConMeta*)(p->dmem + ex.meta);
+    ContractDims d = oi.con;
+    d.tuples = p->d_tuples;
+    d.goff = p->d_goff;
+    d.blk_a = p->d_blk[d.a_op];
+    d.blk_b = p->d_blk[1 - d.a_op];
+    d.blk_c = p->d_blk[2];
+    EA_HIP_TRY(launch_contract_prep(p->con, d, (ConMeta*)(p->dmem + ex.meta), (ConWork*)(p->dmem + ex.work),
+                                    p->d_count, p->tuple_cap, s));
     EA_HIP_TRY(hipStreamSynchronize(s));
   }
   if (oi.kind == K_ATTENTION) {
@@ -1756,23 +1908,13 @@ int run_planned(const Plan* plan, int32_t join_op, int32_t n_in, const ea_relati
       EA_HIP_TRY(launch_gemm(a, s));
       break;
     }
-    case K_GEMM32: {
-      Gemm32Args a;
-      memset(&a, 0, sizeof(a));
-      a.tuples = plan->d_tuples;
-      a.goff = plan->d_goff;
-      a.blk_a = plan->d_blk[0];
-      a.blk_b = plan->d_blk[1];
-      a.blk_c = plan->d_blk[2];
-      a.a = (const char*)in[0]->data;
-      a.b = (const char*)in[1]->data;
+    case K_CONTRACT: {
+      ContractArgs a = plan->con;
+      a.a = (const char*)in[plan->con_a]->data;
+      a.b = (const char*)in[1 - plan->con_a]->data;
       a.c = (char*)out->data;
-      a.work = (const Gemm32Work*)plan->d_work;
-      a.n_work = plan->n_work;
-      a.tuple_stride = 3;
-      a.b_kmajor = plan->b_kmajor;
-      a.dt_out = out->dtype;
-      EA_HIP_TRY(launch_gemm32(a, s));
+      a.res = res ? (const char*)res->data : nullptr;
+      EA_HIP_TRY(launch_contract(a, s));
       break;
     }
     case K_RMSNORM:

@@ -231,31 +231,68 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s);
 hipError_t launch_gemm_prep(const GemmArgs& a, GemmUnit* units, int64_t tuple_cap, hipStream_t s);
 
 // ---------------------------------------------------------------------------
-// fp32 block product "ab,bc->ac" / "ab,cb->ac" on the vector ALUs: a workgroup
-// owns a kGemm32Tile-square tile of one output block and sums its key's tuples.
+// Two-operand contraction on the fp32 matrix cores: one contracted letter, at
+// most one row letter (A, output), one column letter (B, output) and
+// kConMaxBatch batch letters (A, B, output), in any order.
 // ---------------------------------------------------------------------------
-constexpr int kGemm32Tile = 32;
-struct Gemm32Work {
-  int32_t block, m0, n0, pad;
+constexpr int kConMaxBatch = 4;
+constexpr int kConWaves = 4;
+
+// One workgroup: an output tile of one batch index of one output block.  The
+// fields after batch are filled at plan time from the join and the block table.
+struct ConWork {
+  int32_t block, m0, n0, batch;
+  int32_t gb;              // the group's first tuple
+  int32_t mext, next;      // output block extents along the row and column letters
+  int32_t som, son;        // and element strides
+  int32_t pad;
+  int64_t coff;            // output block byte offset
+  int32_t bext[kConMaxBatch], obs[kConMaxBatch];  // batch extents and output strides
+};
+static_assert(sizeof(ConWork) == 80, "ConWork layout");
+
+// One tuple: operand block byte offsets, contracted extent, element strides.
+struct ConMeta {
+  int64_t aoff, boff;
+  int32_t kext, asr, ask, bsr, bsk, pad;
+  int32_t abs_[kConMaxBatch], bbs[kConMaxBatch];  // batch strides
+};
+static_assert(sizeof(ConMeta) == 72, "ConMeta layout");
+
+struct ContractArgs {
+  const char* a;
+  const char* b;
+  char* c;
+  const char* res;       // residual relation data (layout and dtype of c) or null
+  const ConWork* work;
+  const ConMeta* meta;
+  int64_t n_work;
+  int32_t nt, n_steps;   // tuples of a group; 32-deep steps of its walk (64 x 64 tiles)
+  int32_t n_batch;
+  int32_t dt_in, dt_out;
+  int32_t tile;          // 16, 32 (operands in registers) or 64 (through LDS)
+  int32_t rmaj_a, rmaj_b;  // 1: the row (column) letter is the operand's contiguous one
+  int32_t vec_a, vec_b;  // 1: aligned vectors of four along the contiguous letter
+  // 16 and 32: wavefront i's run of k groups, from group g of tuple t of the walk
+  struct Run { int32_t t, g, n; } run[kConWaves];
 };
 
-struct Gemm32Args {
+// Dims of the letters in each operand (-1: absent), for the plan-time kernels.
+struct ContractDims {
   const int32_t* tuples;
   const int32_t* goff;
   const DevBlk* blk_a;
   const DevBlk* blk_b;
   const DevBlk* blk_c;
-  const char* a;
-  const char* b;
-  char* c;
-  const Gemm32Work* work;
-  int64_t n_work;
-  int32_t tuple_stride;
-  int32_t b_kmajor;  // 1: B blocks are [n][k] ("ab,cb->ac")
-  int32_t dt_out;    // EA_F32, EA_BF16 or EA_F16
+  int32_t a_op;          // input that is A (the one with the row letter)
+  int32_t a_rank, b_rank, c_rank;
+  int32_t am, ak, bk, bn, cm, cn;
+  int32_t ab[kConMaxBatch], bb[kConMaxBatch], cb[kConMaxBatch];
 };
 
-hipError_t launch_gemm32(const Gemm32Args& a, hipStream_t s);
+hipError_t launch_contract(const ContractArgs& a, hipStream_t s);
+hipError_t launch_contract_prep(const ContractArgs& a, const ContractDims& d, ConMeta* meta, ConWork* work,
+                                const int32_t* count, int64_t tuple_cap, hipStream_t s);
 
 // ---------------------------------------------------------------------------
 // Row reductions.  A row is the concatenation of its segments, one per tuple
