@@ -11,26 +11,44 @@
 // recompose step is the store into the output block.
 //
 // Inputs bf16 or f16, fp32 accumulation (v_mfma_f32_32x32x16_{bf16,f16}).
-// 512 threads = 8 waves in a 2 (rows) x 4 (columns) grid, two waves per SIMD
-// so that one wave's LDS reads overlap the other's MFMAs.  Tile 256 x 256
-// (each wave 128 x 64: 4 x 2 MFMA tiles, 128 accumulators), or 256 x 128
-// (each wave 128 x 32), which a plan takes when 256-wide tiles would leave
-// CUs idle or need split sums; for SwiGLU 256 x 128 with two right operands
-// (each wave 128 x 32 per operand).
+// Tiles of two heights, chosen per plan by a time model in the host code:
+//   * 256 rows, 512 threads = 8 waves in a 2 (rows) x 4 (columns) grid, two
+//     waves per SIMD so that one wave's LDS reads overlap the other's MFMAs.
+//     256 x 256 (each wave 128 x 64: 4 x 2 MFMA tiles, 128 accumulators), or
+//     256 x 128 (each wave 128 x 32), which a plan takes when 256-wide tiles
+//     would leave CUs idle or need split sums; for SwiGLU 256 x 128 with two
+//     right operands (each wave 128 x 32 per operand).  The fewest operand
+//     bytes per MFMA: the large products.
+//   * 128 rows, 256 threads = 4 waves in a 2 x 2 grid, 128 x 128 (each wave
+//     64 x 64; SwiGLU 128 x 64 of each operand), two workgroups per CU.  Small
+//     and middle products, which 256-row tiles leave with few workgroups or
+//     split into partial sums of 256 KiB.  Bound by the load path at full
+//     occupancy (64 B per clock and CU against the 58 it delivers), by one
+//     wave's step time with one workgroup per CU.  GPU time, bf16 in
+//     512-blocks, 256-row plan -> 128-row plan:
+//       64 x 4096 x 4096     35 -> 17 us     1024 x 1024 x 1024  18.5 -> 12 us
+//       1001 x 2744 x 2008   36 -> 27 us     2048 x 2048 x 2048  32 -> 24 us
+//       1024 x 4096 x 4096   59 -> 43 us     4096 x 4096 x 4096  114 | 154 us
 //
 // Two K pipelines share the tile layout and the epilogue:
-//   * gemm_dl_kernel (every contracted block extent a multiple of 32): operands
-//     go straight from global memory into LDS (global_load_lds_dwordx4), four
-//     stages of 32-deep K steps in flight, XOR-swizzled LDS chunks, [k][n]
-//     right operands read with transposing LDS reads (description below);
-//   * gemm_kernel (any 8-aligned extents): register-staged loads two K steps
-//     ahead, K step 64, LDS double-buffered with padded rows; a right operand
-//     stored [k][n] is transposed in registers before the LDS write.
+//   * gemm_dl_kernel: operands go straight from global memory into LDS
+//     (global_load_lds_dwordx4), four stages of 32-deep K steps in flight,
+//     XOR-swizzled LDS chunks, [k][n] right operands read with transposing LDS
+//     reads (description below).  A contracted block extent that is no
+//     multiple of 32 ends in a partial step;
+//   * gemm_kernel: register-staged loads two K steps ahead, K step 64, LDS
+//     double-buffered with padded rows; a right operand stored [k][n] is
+//     transposed in registers before the LDS write.  For what the direct loads
+//     do not take: more tuples per output block than their LDS table holds, or
+//     operand blocks of 4 GiB and more (1001 x 2744 x 2008, f16: 52 us here,
+//     36 us with direct loads into the same tiles).
 //
 // Epilogue: the tile is staged through LDS so that stores (and the residual
 // loads) are 16-byte row chunks; the residual is added in fp32 before the one
 // rounding to the output dtype; SwiGLU stores silu(g) * u of its two
 // accumulators.
+#include <type_traits>
+
 #include "ea_device.h"
 
 namespace ea {
@@ -180,16 +198,18 @@ struct EpiArgs {
 // Epilogue through LDS.  Accumulator r of MFMA tile (i, j) in lane l holds
 // row 8*(r/4) + 4*(l/32) + r%4 and column l%32 of that 32x32 tile, so a lane
 // owns scattered 2-byte outputs.  The tile's values (SwiGLU: silu(g) * u) are
-// therefore staged in LDS, in four passes of 64 rows (MFMA row-tile i of every
-// wave), fp32 with a row pitch of kEpiPitch floats; then each thread takes 8
+// therefore staged in LDS, in passes of 64 rows (MFMA row-tile i of
+// every wave), fp32 with a row pitch of kEpiPitch floats; then each thread takes 8
 // consecutive columns of one row and stores them with one 16-byte access (two
 // for fp32), reading the residual the same way.  Block rows are multiples of
 // 8 elements on this path (host guarantee), so a chunk never straddles a row.
-constexpr int kEpiPitch = 264;  // 256 + 8: rows 4 apart land on opposite halves of the 64 banks
+template <int W>
+constexpr int kEpiPitch = W == 8 ? 264 : 136;  // columns + 8: rows 4 apart land on opposite halves of the 64 banks
 
-template <bool SWIGLU, int NB, int WN, int W, int DT, bool RES>
-__device__ __forceinline__ void epilogue(const f32x16_t (&acc)[NB][4][WN], const EpiArgs& e, float* stage,
+template <bool SWIGLU, int NB, int MT, int WN, int W, int DT, bool RES>
+__device__ __forceinline__ void epilogue(const f32x16_t (&acc)[NB][MT][WN], const EpiArgs& e, float* stage,
                                          int wid, int lane) {
+  constexpr int PITCH_E = kEpiPitch<W>;
   constexpr int WGN = W / 2;            // waves along n (2 along m)
   constexpr int WCOLS = WN * 32;        // columns per wave
   constexpr int CPR = WGN * WCOLS / 8;  // 8-column chunks per tile row
@@ -202,17 +222,17 @@ __device__ __forceinline__ void epilogue(const f32x16_t (&acc)[NB][4][WN], const
     const int c = tid + 64 * W * k;
     row = c / CPR;
     c8 = c % CPR;
-    gm = e.m0 + (row >> 5) * 128 + 32 * i + (row & 31);
+    gm = e.m0 + (row >> 5) * (32 * MT) + 32 * i + (row & 31);
     gn = e.n0 + 8 * c8;
   };
   // A 16-bit residual is loaded for all four passes before the first one
   // (64 registers), so that one memory latency covers the whole epilogue
   // instead of one per pass; an fp32 residual is loaded pass by pass.
   constexpr bool RES16 = RES && DT != EA_F32;
-  uint4 rres[RES16 ? 4 : 1][RES16 ? CHUNKS : 1];
+  uint4 rres[RES16 ? MT : 1][RES16 ? CHUNKS : 1];
   if constexpr (RES16) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < MT; ++i)
 #pragma unroll
       for (int k = 0; k < CHUNKS; ++k) {
         int row, c8, gm, gn;
@@ -223,7 +243,7 @@ __device__ __forceinline__ void epilogue(const f32x16_t (&acc)[NB][4][WN], const
       }
   }
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
+  for (int i = 0; i < MT; ++i) {
     __syncthreads();  // the stage area is free (K loop or previous pass done)
 #pragma unroll
     for (int j = 0; j < WN; ++j)
@@ -234,7 +254,7 @@ __device__ __forceinline__ void epilogue(const f32x16_t (&acc)[NB][4][WN], const
         // rounded division, far below the output's bf16 rounding
         if constexpr (SWIGLU) v = v * __builtin_amdgcn_rcpf(1.0f + __expf(-v)) * acc[NB - 1][i][j][r];
         const int row = wm * 32 + 8 * (r >> 2) + 4 * g + (r & 3);
-        stage[row * kEpiPitch + wn * WCOLS + 32 * j + lq] = v;
+        stage[row * PITCH_E + wn * WCOLS + 32 * j + lq] = v;
       }
     __syncthreads();
 #pragma unroll
@@ -242,8 +262,8 @@ __device__ __forceinline__ void epilogue(const f32x16_t (&acc)[NB][4][WN], const
       int row, c8, gm, gn;
       chunk_pos(i, k, row, c8, gm, gn);
       if (gm < e.mext && gn < e.next) {
-        const float4 lo = *reinterpret_cast<const float4*>(stage + row * kEpiPitch + 8 * c8);
-        const float4 hi = *reinterpret_cast<const float4*>(stage + row * kEpiPitch + 8 * c8 + 4);
+        const float4 lo = *reinterpret_cast<const float4*>(stage + row * PITCH_E + 8 * c8);
+        const float4 hi = *reinterpret_cast<const float4*>(stage + row * PITCH_E + 8 * c8 + 4);
         float o[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
         const int64_t idx = (int64_t)gm * e.next + gn;
         if constexpr (DT == EA_F32) {
@@ -298,8 +318,8 @@ struct KStep {
 // Then the epilogue, with dtype and residual decided outside its unrolled loops.
 constexpr int32_t kWritten = 1 << 16;         // added by the first of two parts once its partial is stored
 constexpr uint64_t kWrittenWaitTicks = 10000000;  // guard on the second's wait: 100 ms of the 100 MHz clock
-template <bool SWIGLU, int NB, int WN, int W>
-__device__ __forceinline__ void finish_tile(f32x16_t (&acc)[NB][4][WN], const GemmArgs& p, const GemmTile& tile,
+template <bool SWIGLU, int NB, int MT, int WN, int W>
+__device__ __forceinline__ void finish_tile(f32x16_t (&acc)[NB][MT][WN], const GemmArgs& p, const GemmTile& tile,
                                             int wid, int lane, float* stage) {
   __shared__ int s_last;
   const int tid = wid * 64 + lane;
@@ -308,7 +328,7 @@ __device__ __forceinline__ void finish_tile(f32x16_t (&acc)[NB][4][WN], const Ge
     // pieces (every store instruction writes whole 128-byte lines) with the
     // sc1 cache policy, which keeps them coherent between the XCDs' L2s; the
     // reader's loads carry it too.  Every lane holds PER_WAVE floats.
-    constexpr int PER_WAVE = NB * 4 * WN * 16;
+    constexpr int PER_WAVE = NB * MT * WN * 16;
     constexpr int WAVE_BYTES = PER_WAVE * 64 * 4;
     constexpr int kCoherent = 16;  // sc1
     auto slot_rsrc = [&](int slot) {
@@ -316,7 +336,7 @@ __device__ __forceinline__ void finish_tile(f32x16_t (&acc)[NB][4][WN], const Ge
                                                0x00020000);
     };
     auto piece = [&](int o, int i, int j, int r4) {  // byte offset of a lane's piece in its wave's area
-      const int q = ((o * 4 + i) * WN + j) * 4 + r4;
+      const int q = ((o * MT + i) * WN + j) * 4 + r4;
       return (uint32_t)(wid * WAVE_BYTES + (q * 64 + lane) * 16);
     };
     int32_t* const counter = p.counters + tile.counter;
@@ -334,7 +354,7 @@ __device__ __forceinline__ void finish_tile(f32x16_t (&acc)[NB][4][WN], const Ge
 #pragma unroll
       for (int o = 0; o < NB; ++o)
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < MT; ++i)
 #pragma unroll
           for (int j = 0; j < WN; ++j)
 #pragma unroll
@@ -373,14 +393,14 @@ __device__ __forceinline__ void finish_tile(f32x16_t (&acc)[NB][4][WN], const Ge
 #pragma unroll
         for (int t = 0; t < BATCH; ++t) {
           const int q = q0 + t;
-          v[t] = __builtin_amdgcn_raw_buffer_load_b128(rs, piece(q / (16 * WN), (q / (4 * WN)) % 4, (q / 4) % WN, q % 4),
+          v[t] = __builtin_amdgcn_raw_buffer_load_b128(rs, piece(q / (4 * MT * WN), (q / (4 * WN)) % MT, (q / 4) % WN, q % 4),
                                                        0, kCoherent);
         }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int t = 0; t < BATCH; ++t) {
           const int q = q0 + t;
-          f32x16_t& c = acc[q / (16 * WN)][(q / (4 * WN)) % 4][(q / 4) % WN];
+          f32x16_t& c = acc[q / (4 * MT * WN)][(q / (4 * WN)) % MT][(q / 4) % WN];
           const int r4 = q % 4;
           c[4 * r4] += __uint_as_float(v[t].x);
           c[4 * r4 + 1] += __uint_as_float(v[t].y);
@@ -400,7 +420,7 @@ __device__ __forceinline__ void finish_tile(f32x16_t (&acc)[NB][4][WN], const Ge
 #pragma unroll
       for (int o = 0; o < NB; ++o)
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < MT; ++i)
 #pragma unroll
           for (int j = 0; j < WN; ++j) acc[o][i][j] = f32x16_t{};
     }
@@ -410,12 +430,12 @@ __device__ __forceinline__ void finish_tile(f32x16_t (&acc)[NB][4][WN], const Ge
   }
   const DevBlk& cb = p.blk_c[tile.block];
   const EpiArgs e{p.c + cb.off, p.res ? p.res + cb.off : nullptr, cb.ext[0], cb.ext[1], tile.m0, tile.n0};
-  if (!e.res && p.dt_out == EA_BF16) epilogue<SWIGLU, NB, WN, W, EA_BF16, false>(acc, e, stage, wid, lane);
-  else if (!e.res && p.dt_out == EA_F32) epilogue<SWIGLU, NB, WN, W, EA_F32, false>(acc, e, stage, wid, lane);
-  else if (p.dt_out == EA_BF16) epilogue<SWIGLU, NB, WN, W, EA_BF16, true>(acc, e, stage, wid, lane);
-  else if (p.dt_out == EA_F32) epilogue<SWIGLU, NB, WN, W, EA_F32, true>(acc, e, stage, wid, lane);
-  else if (!e.res) epilogue<SWIGLU, NB, WN, W, EA_F16, false>(acc, e, stage, wid, lane);
-  else epilogue<SWIGLU, NB, WN, W, EA_F16, true>(acc, e, stage, wid, lane);
+  if (!e.res && p.dt_out == EA_BF16) epilogue<SWIGLU, NB, MT, WN, W, EA_BF16, false>(acc, e, stage, wid, lane);
+  else if (!e.res && p.dt_out == EA_F32) epilogue<SWIGLU, NB, MT, WN, W, EA_F32, false>(acc, e, stage, wid, lane);
+  else if (p.dt_out == EA_BF16) epilogue<SWIGLU, NB, MT, WN, W, EA_BF16, true>(acc, e, stage, wid, lane);
+  else if (p.dt_out == EA_F32) epilogue<SWIGLU, NB, MT, WN, W, EA_F32, true>(acc, e, stage, wid, lane);
+  else if (!e.res) epilogue<SWIGLU, NB, MT, WN, W, EA_F16, false>(acc, e, stage, wid, lane);
+  else epilogue<SWIGLU, NB, MT, WN, W, EA_F16, true>(acc, e, stage, wid, lane);
 }
 
 template <bool BF16, bool KMAJOR, bool SWIGLU, int W>
@@ -533,8 +553,8 @@ __global__ __launch_bounds__(W * 64, 1) void gemm_kernel(const GemmArgs p) {
     }
   }
 
-  static_assert(sizeof(sA) >= 64 * kEpiPitch * sizeof(float), "epilogue stage");
-  finish_tile<SWIGLU, NB, WN, W>(acc, p, tile, wid, lane, reinterpret_cast<float*>(&sA[0][0]));
+  static_assert(sizeof(sA) >= 64 * kEpiPitch<W> * sizeof(float), "epilogue stage");
+  finish_tile<SWIGLU, NB, 4, WN, W>(acc, p, tile, wid, lane, reinterpret_cast<float*>(&sA[0][0]));
 }
 
 // ===========================================================================
@@ -557,8 +577,9 @@ __global__ __launch_bounds__(W * 64, 1) void gemm_kernel(const GemmArgs p) {
 //     reads 4 columns N0+4r.. of row K0+k', and lane i receives rows K0..K0+3
 //     of column N0+i.
 // Rows or columns past a block's edge load from the block base instead (their
-// products land only in accumulator rows/columns that are never stored); the
-// K extent of every contracted block must be a multiple of 32.
+// products land only in accumulator rows/columns that are never stored), and so
+// do k values past the block in a partial last step, whose pieces are zeroed in
+// LDS before the stage is published (both operands: 0 x NaN is no zero).
 // ===========================================================================
 constexpr int DK = 32;  // K per stage
 constexpr int NSTAGE = 4;
@@ -571,9 +592,14 @@ typedef short s16x4 __attribute__((ext_vector_type(4)));
 // bits 2..3 (their quad indices, 0 3 5 6 or 1 2 4 7, are distinct mod 4), so
 // XOR-ing those bits into the chunk gives each quad its own chunk column.
 __device__ __forceinline__ int swz_row(int r) { return (r >> 2) & 3; }
-// [k][n] rows (a multiple of 256 bytes): the 4 k rows of one transposed read
-// take disjoint chunk sets, for each half of the 32 lanes and for all 32.
-__device__ __forceinline__ int swz_k(int k) { return (2 * (k & 3)) ^ (8 * (k & 1)); }
+// [k][n] rows of BN columns: the 4 k rows of one transposed read take disjoint
+// chunk sets, for each half of the 32 lanes and for all 32 (rows of a multiple
+// of 256 bytes); 64-column rows are 128 bytes, so odd rows lie 128 bytes apart
+// and every second pair swaps its halves.
+template <int BN>
+__device__ __forceinline__ int swz_k(int k) {
+  return BN >= 128 ? (2 * (k & 3)) ^ (8 * (k & 1)) : 4 * ((k >> 1) & 1);
+}
 
 // One direct global->LDS load: each lane fetches 16 bytes at base + voff and
 // the wave's 64 pieces land contiguously at LDS byte address lds_addr
@@ -635,11 +661,17 @@ __device__ __forceinline__ void stage_barrier() {
   __builtin_amdgcn_sched_barrier(0);
 }
 
-template <bool BF16, bool KMAJOR, bool SWIGLU, bool NARROW, int W>
-__global__ __launch_bounds__(64 * W, 1) void gemm_dl_kernel(const GemmArgs p) {
+// W: 8 waves and 256-row tiles, or 4 waves and 128-row tiles (two workgroups
+// per CU).  TAIL: some contracted block extent is no multiple of 32; the last
+// K step of such a block is part of one: lanes whose k lies past the block
+// load from its start instead, and zero their pieces in LDS once landed.
+template <bool BF16, bool KMAJOR, bool SWIGLU, bool NARROW, bool TAIL, int W>
+__global__ __launch_bounds__(64 * W, W == 8 ? 1 : 2) void gemm_dl_kernel(const GemmArgs p) {
   constexpr int WGN = W / 2;                         // waves along n (2 along m)
   constexpr int NB = SWIGLU ? 2 : 1;                 // right operands
-  constexpr int BN = SWIGLU || NARROW ? 128 : 256;  // columns per right operand
+  constexpr int TM = W * 32;                         // tile rows
+  constexpr int MT = TM / 64;                        // MFMA tiles per wave along m
+  constexpr int BN = (SWIGLU || NARROW ? 128 : 256) / (8 / W);  // columns per right operand
   constexpr int WCOLS = BN / WGN;              // columns per wave, per operand
   constexpr int WN = WCOLS / 32;               // MFMA tiles per wave along n, per operand
   constexpr int A_ELEMS = TM * DK;             // per stage
@@ -679,11 +711,11 @@ __global__ __launch_bounds__(64 * W, 1) void gemm_dl_kernel(const GemmArgs p) {
   for (int i = tid; i < nt; i += 64 * W) s_meta[i] = p.meta[gb + i];
   __syncthreads();
 
-  f32x16_t acc[NB][4][WN];
+  f32x16_t acc[NB][MT][WN];
 #pragma unroll
   for (int o = 0; o < NB; ++o)
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < MT; ++i)
 #pragma unroll
       for (int j = 0; j < WN; ++j) acc[o][i][j] = f32x16_t{};
 
@@ -706,6 +738,10 @@ __global__ __launch_bounds__(64 * W, 1) void gemm_dl_kernel(const GemmArgs p) {
   uint32_t va[LA], vb[NB][LBO];
   uint32_t bstep[NB];
   int left = 0;
+  // TAIL: the current tuple's k values in its last step if that is partial,
+  // else 0; and per stage (a byte each) how many k values its step holds
+  int tail = 0;
+  uint32_t held = 0;
   auto set_tuple = [&](int t) {
     const GemmTupleMeta& m = s_meta[t];
     a_base = p.a + m.aoff;
@@ -733,79 +769,125 @@ __global__ __launch_bounds__(64 * W, 1) void gemm_dl_kernel(const GemmArgs p) {
 #pragma unroll
         for (int q = 0; q < LBO; ++q) {
           const int k = (wid * LBO + q) * RPI + lane / CPR;
-          const int c = (lane % CPR) ^ swz_k(k);
+          const int c = (lane % CPR) ^ swz_k<BN>(k);
           const int gn = tile.n0 + 8 * c;
           vb[o][q] = (uint32_t)(((int64_t)k * e1 + (gn < e1 ? gn : 0)) * 2);
         }
         bstep[o] = (uint32_t)(DK * e1 * 2);
       }
     }
-    left = m.ak / DK;
+    left = TAIL ? (m.ak + DK - 1) / DK : m.ak / DK;
+    if constexpr (TAIL) tail = m.ak % DK;
   };
   auto seek = [&]() {  // first tuple at or after it_t with a K step
-    while (it_t < nt && s_meta[it_t].ak < DK) ++it_t;
+    while (it_t < nt && s_meta[it_t].ak < 1) ++it_t;
     if (it_t < nt) set_tuple(it_t);
   };
-  // issue the loads of the next K step of the walk into stage u
-  auto issue_next = [&](int u) {
+  // the k offset of a lane's piece inside its step, for A (and [n][k] B) loads
+  // and for [k][n] B loads
+  auto row_k = [&](int q, int per) {
+    const int r = (wid * per + q) * 16 + (lane >> 2);
+    return 8 * ((lane & 3) ^ swz_row(r));
+  };
+  auto b_k = [&](int q) { return KMAJOR ? row_k(q, LBO) : (wid * LBO + q) * RPI + lane / CPR; };
+  // issue load i of this wave's share of the next K step of the walk into stage
+  // u (i < LA: A, then each right operand); after the last, next_step
+  bool part = false;  // the step is partial (TAIL)
+  auto issue_piece = [&](int u, int i) {
     const uint32_t sbase = lds_base + (uint32_t)(u * STAGE * 2);
-#pragma unroll
-    for (int q = 0; q < LA; ++q) {
-      dl_load16(a_base, va[q], sbase + (uint32_t)((wid * LA + q) * 1024));
-      va[q] += DK * 2;
+    if (i < LA) {
+      uint32_t v = va[i];
+      if (part) v = row_k(i, LA) < tail ? v : 0;
+      dl_load16(a_base, v, sbase + (uint32_t)((wid * LA + i) * 1024));
+      va[i] += DK * 2;
+    } else {
+      const int o = (i - LA) / LBO, q = (i - LA) % LBO;
+      uint32_t v = vb[o][q];
+      if (part) v = b_k(q) < tail ? v : 0;
+      dl_load16(b_base[o], v, sbase + (uint32_t)(A_ELEMS * 2 + o * B_ELEMS * 2 + (wid * LBO + q) * 1024));
+      vb[o][q] += bstep[o];
     }
-#pragma unroll
-    for (int o = 0; o < NB; ++o)
-#pragma unroll
-      for (int q = 0; q < LBO; ++q) {
-        dl_load16(b_base[o], vb[o][q], sbase + (uint32_t)(A_ELEMS * 2 + o * B_ELEMS * 2 + (wid * LBO + q) * 1024));
-        vb[o][q] += bstep[o];
-      }
+  };
+  auto begin_step = [&](int u) {
+    if constexpr (TAIL) {
+      part = left == 1 && tail > 0;
+      held = (held & ~(255u << (8 * u))) | ((uint32_t)(part ? tail : DK) << (8 * u));
+    }
+  };
+  auto next_step = [&]() {
     if (--left == 0) {
       ++it_t;
       seek();
     }
   };
+  auto issue_next = [&](int u) {
+    begin_step(u);
+#pragma unroll
+    for (int i = 0; i < LS; ++i) issue_piece(u, i);
+    next_step();
+  };
+  // a partial step's masked pieces of this wave, once its loads have landed
+  // (and before the barrier that publishes the stage)
+  auto zero_tail = [&](int u) {
+    if constexpr (TAIL) {
+      const int valid = (int)((held >> (8 * u)) & 255u);
+      if (valid < DK) {
+        uint16_t* st = smem + u * STAGE;
+        const uint4 zero = make_uint4(0, 0, 0, 0);
+#pragma unroll
+        for (int q = 0; q < LA; ++q)
+          if (row_k(q, LA) >= valid) *reinterpret_cast<uint4*>(st + (wid * LA + q) * 512 + lane * 8) = zero;
+#pragma unroll
+        for (int o = 0; o < NB; ++o)
+#pragma unroll
+          for (int q = 0; q < LBO; ++q)
+            if (b_k(q) >= valid)
+              *reinterpret_cast<uint4*>(st + A_ELEMS + o * B_ELEMS + (wid * LBO + q) * 512 + lane * 8) = zero;
+      }
+    }
+  };
 
   // ---- MFMA operands of one 16-deep half of a stage
   struct Frag {
-    uint4 a[4];
+    uint4 a[MT];
     uint4 b[NB][WN];
   };
-  auto load_frag = [&](Frag& f, int u, int s) {
+  auto read_a = [&](Frag& f, int u, int s, int i) {
     const uint16_t* sa = smem + u * STAGE;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int r = wm * 128 + i * 32 + lq;
+    const int r = wm * (TM / 2) + i * 32 + lq;
+    const int c = (2 * s + g) ^ swz_row(r);
+    f.a[i] = *reinterpret_cast<const uint4*>(sa + r * DK + 8 * c);
+  };
+  auto read_b = [&](Frag& f, int u, int s, int o, int j) {
+    const uint16_t* sbo = smem + u * STAGE + A_ELEMS + o * B_ELEMS;
+    if constexpr (KMAJOR) {
+      const int r = wn * WCOLS + j * 32 + lq;
       const int c = (2 * s + g) ^ swz_row(r);
-      f.a[i] = *reinterpret_cast<const uint4*>(sa + r * DK + 8 * c);
+      f.b[o][j] = *reinterpret_cast<const uint4*>(sbo + r * DK + 8 * c);
+    } else {
+      const int gq = lane >> 4, li = lane & 15;
+      const int n = wn * WCOLS + j * 32 + 16 * (gq & 1) + 4 * (li & 3);
+      uint2 h2[2];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int k = 16 * s + 8 * (gq >> 1) + 4 * h + (li >> 2);
+        const int c = (n >> 3) ^ swz_k<BN>(k);
+        h2[h] = tr_read(sbo + k * BN + 8 * c + (n & 4));
+      }
+      f.b[o][j] = make_uint4(h2[0].x, h2[0].y, h2[1].x, h2[1].y);
     }
+  };
+  auto load_frag = [&](Frag& f, int u, int s) {
+#pragma unroll
+    for (int i = 0; i < MT; ++i) read_a(f, u, s, i);
 #pragma unroll
     for (int o = 0; o < NB; ++o)
 #pragma unroll
-      for (int j = 0; j < WN; ++j) {
-        const uint16_t* sbo = sa + A_ELEMS + o * B_ELEMS;
-        if constexpr (KMAJOR) {
-          const int r = wn * WCOLS + j * 32 + lq;
-          const int c = (2 * s + g) ^ swz_row(r);
-          f.b[o][j] = *reinterpret_cast<const uint4*>(sbo + r * DK + 8 * c);
-        } else {
-          const int gq = lane >> 4, li = lane & 15;
-          const int n = wn * WCOLS + j * 32 + 16 * (gq & 1) + 4 * (li & 3);
-          uint2 h2[2];
-#pragma unroll
-          for (int h = 0; h < 2; ++h) {
-            const int k = 16 * s + 8 * (gq >> 1) + 4 * h + (li >> 2);
-            const int c = (n >> 3) ^ swz_k(k);
-            h2[h] = tr_read(sbo + k * BN + 8 * c + (n & 4));
-          }
-          f.b[o][j] = make_uint4(h2[0].x, h2[0].y, h2[1].x, h2[1].y);
-        }
-      }
+      for (int j = 0; j < WN; ++j) read_b(f, u, s, o, j);
   };
   auto mma = [&](const Frag& f) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < MT; ++i)
 #pragma unroll
       for (int o = 0; o < NB; ++o)
 #pragma unroll
@@ -849,30 +931,113 @@ __global__ __launch_bounds__(64 * W, 1) void gemm_dl_kernel(const GemmArgs p) {
       for (int q = 0; q < LBO; ++q) vb[o][q] += (uint32_t)skip * bstep[o];
     left -= skip;
   }
-  const int n_pro = n_steps < D ? n_steps : D;
-  for (int st = 0; st < n_pro; ++st) issue_next(st);
-  if (n_steps > 0) {
-    wait_after(n_pro - 1);
-    stage_barrier();
-    if (grp == 1) stage_barrier();  // waves 4-7 start one phase behind
-    Frag f0, f1;
-    for (int k = 0; k < n_steps; ++k) {
-      const int u = k % NSTAGE;
-      if (k + D < n_steps) issue_next((k + D) % NSTAGE);
-      load_frag(f0, u, 0);
-      load_frag(f1, u, 1);
-      const int later = (k + D < n_steps ? k + D : n_steps - 1) - (k + 1);
-      if (grp == 1 && k + 1 < n_steps) wait_after(later);
-      stage_barrier();  // lgkmcnt(0): operands in registers, stage u read
-      mma(f0);
-      mma(f1);
-      if (grp == 0 && k + 1 < n_steps) wait_after(later);
+  if constexpr (W == 8) {
+    const int n_pro = n_steps < D ? n_steps : D;
+    for (int st = 0; st < n_pro; ++st) issue_next(st);
+    if (n_steps > 0) {
+      wait_after(n_pro - 1);
+      zero_tail(0);
       stage_barrier();
+      if (grp == 1) stage_barrier();  // waves 4-7 start one phase behind
+      Frag f0, f1;
+      for (int k = 0; k < n_steps; ++k) {
+        const int u = k % NSTAGE;
+        if (k + D < n_steps) issue_next((k + D) % NSTAGE);
+        load_frag(f0, u, 0);
+        load_frag(f1, u, 1);
+        const int later = (k + D < n_steps ? k + D : n_steps - 1) - (k + 1);
+        if (grp == 1 && k + 1 < n_steps) {
+          wait_after(later);
+          zero_tail((k + 1) % NSTAGE);
+        }
+        stage_barrier();  // lgkmcnt(0): operands in registers, stage u read
+        mma(f0);
+        mma(f1);
+        if (grp == 0 && k + 1 < n_steps) {
+          wait_after(later);
+          zero_tail((k + 1) % NSTAGE);
+        }
+        stage_barrier();
+      }
+      if (grp == 0) stage_barrier();  // ... and waves 0-3 end one phase early
     }
-    if (grp == 0) stage_barrier();  // ... and waves 0-3 end one phase early
+  } else {
+    // Four waves, two workgroups per CU (their barriers are independent, so
+    // one computes while the other waits).  Step k's operands are read into
+    // registers while step k-1's MFMAs run, which frees stage k at the next
+    // barrier: all four stages hold steps in flight or being read.  At the
+    // barrier of step k every wave has waited for its own loads of step k+1
+    // and finished its reads of stage k, so after it step k+4 may overwrite
+    // stage k and step k+1 may be read.
+    const int n_pro = n_steps < NSTAGE ? n_steps : NSTAGE;
+    for (int st = 0; st < n_pro; ++st) issue_next(st);
+    if (n_steps > 0) {
+      if (n_pro == NSTAGE) wait_vmcnt<3 * LS>();
+      else wait_after(n_pro - 1);
+      zero_tail(0);
+      stage_barrier();
+      Frag f[2][2];
+      load_frag(f[0][0], 0, 0);
+      load_frag(f[0][1], 0, 1);
+      // One MFMA of the step at a time, with the next operands' reads and the
+      // loads between them: a wave issuing a load or an LDS read waits under
+      // its own running MFMAs.  The first ones run while the wave waits for its
+      // loads and at the barrier.  FULL: steps k+1 .. k+4 exist.
+      constexpr int NM = 2 * MT * NB * WN;  // MFMAs of a step
+      static_assert(NM == 8 && LS <= 4, "interleave below");
+      auto mm = [&](const Frag (&x)[2], int e) {
+        const int hf = e / (NM / 2), q = e % (NM / 2), i = q / (NB * WN), o = (q / WN) % NB, j = q % WN;
+        acc[o][i][j] = mfma<BF16>(x[hf].a[i], x[hf].b[o][j], acc[o][i][j]);
+      };
+      auto step = [&](int k, auto cur_tag, auto full_tag) __attribute__((always_inline)) {
+        constexpr int cur = decltype(cur_tag)::value;
+        constexpr bool FULL = decltype(full_tag)::value;
+        const bool more = FULL || k + 1 < n_steps;
+        const int u1 = (k + 1) % NSTAGE;
+        mm(f[cur], 0);
+        mm(f[cur], 1);
+        if (more) {
+          if constexpr (FULL) wait_vmcnt<2 * LS>();
+          else wait_after(min(n_steps - 1, k + NSTAGE - 1) - (k + 1));
+          zero_tail(u1);
+        }
+        stage_barrier();
+        if (more) load_frag(f[cur ^ 1][0], u1, 0);
+        mm(f[cur], 2);
+        __builtin_amdgcn_sched_barrier(0);
+        if (more) load_frag(f[cur ^ 1][1], u1, 1);
+        mm(f[cur], 3);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (FULL) {
+          begin_step(k % NSTAGE);
+#pragma unroll
+          for (int i = 0; i < LS; ++i) {
+            issue_piece(k % NSTAGE, i);
+            mm(f[cur], 4 + i);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+#pragma unroll
+          for (int e = 4 + LS; e < NM; ++e) mm(f[cur], e);
+          next_step();
+        } else {
+#pragma unroll
+          for (int e = 4; e < NM; ++e) mm(f[cur], e);
+        }
+      };
+      int k = 0;
+      for (; k + 1 + NSTAGE < n_steps; k += 2) {  // (an even count, so that the rest starts on set 0)
+        step(k, std::integral_constant<int, 0>{}, std::true_type{});
+        step(k + 1, std::integral_constant<int, 1>{}, std::true_type{});
+      }
+      for (; k < n_steps; k += 2) {
+        if (k + NSTAGE < n_steps) step(k, std::integral_constant<int, 0>{}, std::true_type{});
+        else step(k, std::integral_constant<int, 0>{}, std::false_type{});
+        if (k + 1 < n_steps) step(k + 1, std::integral_constant<int, 1>{}, std::false_type{});
+      }
+    }
   }
-  static_assert(sizeof(smem) >= 64 * kEpiPitch * sizeof(float), "epilogue stage");
-  finish_tile<SWIGLU, NB, WN, W>(acc, p, tile, wid, lane, reinterpret_cast<float*>(smem));
+  static_assert(sizeof(smem) >= 64 * kEpiPitch<W> * sizeof(float), "epilogue stage");
+  finish_tile<SWIGLU, NB, MT, WN, W>(acc, p, tile, wid, lane, reinterpret_cast<float*>(smem));
   };
   run_segment(unit->seg[0]);
   if (unit->n_seg > 1) {
@@ -884,13 +1049,18 @@ __global__ __launch_bounds__(64 * W, 1) void gemm_dl_kernel(const GemmArgs p) {
 
 template <bool BF16, bool KMAJOR, bool SWIGLU>
 hipError_t launch3(const GemmArgs& a, hipStream_t s) {
-  if (a.direct && !SWIGLU && a.tile_n == 128)
-    hipLaunchKernelGGL((gemm_dl_kernel<BF16, KMAJOR, false, true, 8>), dim3((uint32_t)a.n_units), dim3(512), 0, s, a);
-  else if (a.direct)
-    hipLaunchKernelGGL((gemm_dl_kernel<BF16, KMAJOR, SWIGLU, false, 8>), dim3((uint32_t)a.n_units), dim3(512), 0, s,
-                       a);
-  else
-    hipLaunchKernelGGL((gemm_kernel<BF16, KMAJOR, SWIGLU, 8>), dim3((uint32_t)a.n_tiles), dim3(512), 0, s, a);
+  const dim3 grid((uint32_t)(a.direct ? a.n_units : a.n_tiles));
+  if (a.direct && a.tile_m == 128) {
+    if (a.tail) hipLaunchKernelGGL((gemm_dl_kernel<BF16, KMAJOR, SWIGLU, false, true, 4>), grid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((gemm_dl_kernel<BF16, KMAJOR, SWIGLU, false, false, 4>), grid, dim3(256), 0, s, a);
+  } else if (a.direct && !SWIGLU && a.tile_n == 128) {
+    if (a.tail) hipLaunchKernelGGL((gemm_dl_kernel<BF16, KMAJOR, false, true, true, 8>), grid, dim3(512), 0, s, a);
+    else hipLaunchKernelGGL((gemm_dl_kernel<BF16, KMAJOR, false, true, false, 8>), grid, dim3(512), 0, s, a);
+  } else if (a.direct) {
+    if (a.tail) hipLaunchKernelGGL((gemm_dl_kernel<BF16, KMAJOR, SWIGLU, false, true, 8>), grid, dim3(512), 0, s, a);
+    else hipLaunchKernelGGL((gemm_dl_kernel<BF16, KMAJOR, SWIGLU, false, false, 8>), grid, dim3(512), 0, s, a);
+  } else
+    hipLaunchKernelGGL((gemm_kernel<BF16, KMAJOR, SWIGLU, 8>), grid, dim3(512), 0, s, a);
   return hipGetLastError();
 }
 
@@ -941,7 +1111,7 @@ __global__ __launch_bounds__(256) void gemm_seg_kernel(const GemmArgs p, GemmUni
   for (int k = 0; k < un.n_seg && k < kGemmMaxSegs; ++k) {
     GemmSeg& sg = un.seg[k];
     const int32_t gb = p.goff[sg.block], nt = p.goff[sg.block + 1] - gb;
-    auto steps = [&](int i) { return p.blk_a[p.tuples[(int64_t)(gb + i) * p.tuple_stride + 1]].ext[1] / DK; };
+    auto steps = [&](int i) { return (p.blk_a[p.tuples[(int64_t)(gb + i) * p.tuple_stride + 1]].ext[1] + DK - 1) / DK; };
     int group_steps = 0;
     for (int i = 0; i < nt; ++i) group_steps += steps(i);
     int t = 0, skip = sg.s0;

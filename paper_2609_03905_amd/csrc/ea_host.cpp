@@ -322,7 +322,9 @@ struct Plan {
   int b_kmajor = 0;
   int gemm_parts = 1;
   bool gemm_direct = false;  // direct-load kernel (work list of GemmUnit), else GemmTile
-  int gemm_tn = kGemmTN;     // output tile columns per right operand (256, or 128)
+  int gemm_tn = kGemmTN;     // output tile columns per right operand (256, 128 or 64)
+  int gemm_tm = kGemmTM;     // output tile rows (256, or 128)
+  bool gemm_tail = false;    // some contracted block extent is no multiple of 32
   GemmTupleMeta* d_gemm_meta = nullptr;  // direct-load plans: per-tuple operand blocks
   // contraction: everything of its arguments but the data pointers
   ContractArgs con;
@@ -845,9 +847,11 @@ struct GemmPlanInfo {
   int parts = 1;
 };
 
-GemmPlanInfo gemm_units(const ea_relation* a, const ea_relation* c, int tn, double step_scale = 1.0) {
+// parts > 0 fixes the split count.
+GemmPlanInfo gemm_units(const ea_relation* a, const ea_relation* c, int tn, double step_scale = 1.0, int tm = kGemmTM,
+                        int parts = 0) {
   const int kCUs = 256;
-  const double tile_bytes = (double)kGemmTM * tn * 4;
+  const double tile_bytes = (double)tm * tn * 4;
   // K steps of a group: every group has the same contracted blocks (a's column blocks)
   int64_t steps = 0;
   const int n_t = a->nb[1];
@@ -858,7 +862,7 @@ GemmPlanInfo gemm_units(const ea_relation* a, const ea_relation* c, int tn, doub
     block_coords(c, b, co);
     const int64_t me = c->splits[0][co[0] + 1] - c->splits[0][co[0]];
     const int64_t ne = c->splits[1][co[1] + 1] - c->splits[1][co[1]];
-    for (int64_t m0 = 0; m0 < me; m0 += kGemmTM)
+    for (int64_t m0 = 0; m0 < me; m0 += tm)
       for (int64_t n0 = 0; n0 < ne; n0 += tn) {
         GemmTile t;
         memset(&t, 0, sizeof(t));
@@ -882,6 +886,7 @@ GemmPlanInfo gemm_units(const ea_relation* a, const ea_relation* c, int tn, doub
       best_p = P;
     }
   }
+  if (parts > 0) best_p = parts;
   GemmPlanInfo info;
   info.parts = best_p;
   std::vector<GemmTile> all;
@@ -910,7 +915,7 @@ GemmPlanInfo gemm_units(const ea_relation* a, const ea_relation* c, int tn, doub
   // every part is spread over all eight.
   std::vector<int> mrow(c->nb[0] + 1, 0), ncol(c->nb[1] + 1, 0);
   for (int b = 0; b < c->nb[0]; ++b)
-    mrow[b + 1] = mrow[b] + (int)((c->splits[0][b + 1] - c->splits[0][b] + kGemmTM - 1) / kGemmTM);
+    mrow[b + 1] = mrow[b] + (int)((c->splits[0][b + 1] - c->splits[0][b] + tm - 1) / tm);
   for (int b = 0; b < c->nb[1]; ++b) ncol[b + 1] = ncol[b] + (int)((c->splits[1][b + 1] - c->splits[1][b] + tn - 1) / tn);
   const int mt = mrow.back(), ntl = ncol.back();
   const int nx = 8;
@@ -935,7 +940,7 @@ GemmPlanInfo gemm_units(const ea_relation* a, const ea_relation* c, int tn, doub
   std::vector<std::vector<Keyed>> q(nx);
   for (const GemmTile& t : all) {
     block_coords(c, t.block, co);
-    const int mi = mrow[co[0]] + t.m0 / kGemmTM, ni = ncol[co[1]] + t.n0 / tn;
+    const int mi = mrow[co[0]] + t.m0 / tm, ni = ncol[co[1]] + t.n0 / tn;
     const int rb = (int)((int64_t)mi * gr / std::max(mt, 1)), cb = (int)((int64_t)ni * gc / std::max(ntl, 1));
     const int region = rb * gc + cb;
     const int x = split_parts ? (t.part * per_part + region) % nx : region % nx;
@@ -961,8 +966,7 @@ GemmPlanInfo gemm_units(const ea_relation* a, const ea_relation* c, int tn, doub
   return info;
 }
 
-// Units of the direct-load kernel (contracted block extents multiples of 32,
-// at most kGemmMaxTuples tuples per group).  Two schedules are costed and the
+// Units of the direct-load kernel (at most kGemmMaxTuples tuples per group).  Two schedules are costed and the
 // cheaper one is kept:
 //   * even: the tiles of gemm_units (split or not, in XCD-aware order), one
 //     segment each;
@@ -998,7 +1002,7 @@ GemmDlPlan gemm_units_dl(const ea_relation* a, const ea_relation* c, int tn, con
   // K-step prefix over a group's tuples (A's contracted blocks, in order)
   const int n_t = a->nb[1];
   std::vector<int32_t> pre(n_t + 1, 0);
-  for (int b = 0; b < n_t; ++b) pre[b + 1] = pre[b] + (int32_t)((a->splits[1][b + 1] - a->splits[1][b]) / 32);
+  for (int b = 0; b < n_t; ++b) pre[b + 1] = pre[b] + (int32_t)((a->splits[1][b + 1] - a->splits[1][b] + 31) / 32);
   const int64_t S = pre[n_t];
   auto merge_bytes = [&](int parts) { return parts > 1 ? (parts == 2 ? 2 : 2 * parts) * tile_bytes : 0.0; };
   // even schedule, as one-segment units
@@ -1194,6 +1198,68 @@ int build_contract(const ea_relation* const* ops, const ContractDims& d, int64_t
   ex->n_work = (int64_t)work.size();
   ex->meta = img->put_zero((size_t)tuple_cap * sizeof(ConMeta));
   return EA_OK;
+}
+
+// Time model (us) of 128-row tiles, each tile's S steps cut into P runs, two
+// workgroups per CU.  Fitted on one card (bf16, 512-blocks, measured | model):
+//   64 x 4096 x 4096    (32 tiles, S 128)  P 1 32.9 | 36   P 2 22.5 | 24   P 4 18.1 | 19   P 6 17.2 | 19
+//   1024 x 1024 x 1024  (64, 32)           P 1 12.0 | 12   P 2 14.2 | 13   P 3 12.5 | 14
+//   512 x 4096 x 4096   (128, 128)         P 1 39.5 | 40   P 2 29.3 | 30   P 3 37.3 | 39
+//   2048 x 2048 x 2048  (256, 64)          P 1 23.6 | 24   P 2 30.9 | 30
+//   1024 x 4096 x 4096  (256, 128)         P 1 42.6 | 44   P 2 49.9 | 48
+//   4096 x 4096 x 1536  (384, 128)         P 1 71.5 | 74   P 2 76.3 | 92
+// A 32-deep step of a workgroup alone on its CU takes 0.25 us, 0.32 when all
+// 256 CUs run one; two workgroups on a CU take 0.55 us for a step of each.
+// 3.5 us per round: launch, pipeline fill, store.  Split sums: 3 us, plus
+// 0.7 us per part where the last arriver re-reads all (three or more), plus
+// the traffic of one 64 KiB partial per unit.
+double gemm_mid_time(int64_t tiles, int64_t S, int P) {
+  const int64_t units = tiles * P, n = (S + P - 1) / P;
+  double t;
+  if (units <= 256) t = 3.5 + (double)n * (0.25 + 0.07 * (double)units / 256.0);
+  else t = std::ceil((double)units / 512.0) * (3.5 + 0.55 * (double)n);
+  if (P > 1) t += 3.0 + (P > 2 ? 0.7 * P : 0.0) + 0.012 * (double)units;
+  return t;
+}
+
+// 128-row tiles on four wavefronts, two workgroups per CU: each tile's K walk
+// cut into P equal runs of 32-deep steps (not only at tuple bounds).
+GemmDlPlan gemm_units_mid(const ea_relation* a, const ea_relation* c, int tn) {
+  int64_t S = 0;
+  for (int b = 0; b < a->nb[1]; ++b) S += (a->splits[1][b + 1] - a->splits[1][b] + 31) / 32;
+  const GemmPlanInfo one = gemm_units(a, c, tn, 1.0, kGemmMidTM, 1);
+  const int64_t tiles = (int64_t)one.units.size();
+  int best_p = 1;
+  double best = 1e300;
+  for (int P = 1; P <= 16 && P <= S && (P == 1 || tiles * P <= 512); ++P) {  // split plans: at most 32 MiB of partials
+    const double t = gemm_mid_time(tiles, S, P);
+    if (t < best - 1e-9) {
+      best = t;
+      best_p = P;
+    }
+  }
+  const GemmPlanInfo gi = gemm_units(a, c, tn, 1.0, kGemmMidTM, best_p);
+  GemmDlPlan out;
+  out.cost = best;
+  out.slots = gi.slots;
+  out.counters = gi.counters;
+  for (const GemmTile& t : gi.units) {
+    GemmUnit u;
+    memset(&u, 0, sizeof(u));
+    GemmSeg& g = u.seg[0];
+    g.block = t.block;
+    g.m0 = t.m0;
+    g.n0 = t.n0;
+    g.s0 = (int32_t)(S * t.part / best_p);
+    g.s1 = (int32_t)(S * (t.part + 1) / best_p);
+    g.part = t.part;
+    g.n_parts = t.n_parts;
+    g.first_slot = t.first_slot;
+    g.counter = t.counter;
+    u.n_seg = 1;
+    out.units.push_back(u);
+  }
+  return out;
 }
 
 int build_rows(const Spec& sp, const ea_relation* const* ops, const OpInfo& oi, Image* img, Extra* ex,
@@ -1439,14 +1505,12 @@ int get_joinagg_plan(const char* spec_str, const Spec& sp, int32_t join_op, int3
     case K_GEMM: {
       const bool swiglu = join_op == EA_OP_SWIGLU;
       int tn = swiglu ? kGemmTNSwiglu : kGemmTN;
-      // direct-to-LDS kernel: contracted block extents multiples of 32, at
-      // most kGemmMaxTuples tuples per group (staged in LDS) and operand
-      // blocks below 4 GiB (32-bit lane offsets); else the register-staged one
-      bool k32 = true;
-      for (int64_t v : ops[0]->splits[1]) k32 &= v % 32 == 0;
+      // direct-to-LDS kernel: at most kGemmMaxTuples tuples per group (staged
+      // in LDS) and operand blocks below 4 GiB (32-bit lane offsets); else the register-staged one
+      for (int64_t v : ops[0]->splits[1]) p->gemm_tail |= v % 32 != 0;
       bool small = true;
       for (int i = 0; i < sp.n_in; ++i) small &= max_block_bytes(ops[i]) < (int64_t(1) << 32);
-      p->gemm_direct = k32 && ops[0]->nb[1] <= kGemmMaxTuples && small;
+      p->gemm_direct = ops[0]->nb[1] <= kGemmMaxTuples && small;
       GemmPlanInfo gi = gemm_units(ops[0], ops[sp.n_in], tn);
       GemmDlPlan dl;
       if (p->gemm_direct) dl = gemm_units_dl(ops[0], ops[sp.n_in], tn, gi);
@@ -1465,6 +1529,23 @@ int get_joinagg_plan(const char* spec_str, const Spec& sp, int32_t join_op, int3
           dl = dn;
         }
       }
+      int64_t slot_bytes = kGemmTM * kGemmTN * (int64_t)sizeof(float);
+      // 128-row tiles where they are estimated cheaper: small and middle sizes,
+      // which 256-row tiles either leave with few workgroups or split into
+      // many partial sums of 256 KiB.  (The 256-row model above leaves out
+      // launch, first loads and store, 5 us on every shape measured.)  The
+      // overrides of the 256-row plans, and EA_GEMM_TILE_M=256, keep those.
+      const char* tile_m = getenv("EA_GEMM_TILE_M");
+      if (p->gemm_direct && !getenv("EA_GEMM_SCHEDULE") && !getenv("EA_GEMM_TILE_N") && !(tile_m && atoi(tile_m) == 256)) {
+        const int mtn = swiglu ? kGemmMidTN / 2 : kGemmMidTN;
+        const GemmDlPlan dm = gemm_units_mid(ops[0], ops[sp.n_in], mtn);
+        if (dm.cost < dl.cost + 5.0 || (tile_m && atoi(tile_m) == 128)) {
+          p->gemm_tm = kGemmMidTM;
+          tn = mtn;
+          dl = dm;
+          slot_bytes = kGemmMidTM * kGemmMidTN * (int64_t)sizeof(float);
+        }
+      }
       p->gemm_tn = tn;
       p->gemm_parts = gi.parts;
       int64_t slots = gi.slots;
@@ -1480,7 +1561,7 @@ int get_joinagg_plan(const char* spec_str, const Spec& sp, int32_t join_op, int3
         p->ws_counters = gi.counters;
       }
       // fp32 partial tiles of split keys in the workspace
-      p->ws_partial_bytes = slots * kGemmTM * kGemmTN * (int64_t)sizeof(float);
+      p->ws_partial_bytes = slots * slot_bytes;
       break;
     }
     case K_CONTRACT: e = build_contract(ops, oi.con, p->tuple_cap, &img, &ex, &p->con); break;
@@ -1891,6 +1972,8 @@ int run_planned(const Plan* plan, int32_t join_op, int32_t n_in, const ea_relati
       a.dt_res = res ? res->dtype : 0;
       a.direct = plan->gemm_direct;
       a.tile_n = plan->gemm_tn;
+      a.tile_m = plan->gemm_tm;
+      a.tail = plan->gemm_tail;
       a.meta = plan->d_gemm_meta;
       if (a.direct) {
         a.units = (const GemmUnit*)plan->d_work;

@@ -150,6 +150,8 @@ hipError_t launch_repartition(const RepTask* d_tasks, int64_t n_tasks, const cha
 constexpr int kGemmTM = 256;          // output tile rows of one workgroup
 constexpr int kGemmTN = 256;          // output tile columns (128 for SwiGLU)
 constexpr int kGemmTNSwiglu = 128;
+constexpr int kGemmMidTM = 128;       // 128-row tiles (four wavefronts): rows
+constexpr int kGemmMidTN = 128;       // and columns (64 of each right operand for SwiGLU)
 constexpr int kGemmMaxTuples = 128;   // tuples per unit on the direct-to-LDS kernel
 
 struct GemmTile {      // one workgroup: a tile of one output block and a run of its tuples
@@ -217,8 +219,10 @@ struct GemmArgs {
   int32_t dt_out;        // EA_F32, EA_BF16 or EA_F16
   int32_t dt_res;
   int32_t swiglu;        // 1: out = silu(A B) * (A B2)
-  int32_t direct;        // 1: direct-to-LDS kernel (contracted block extents multiples of 32)
+  int32_t direct;        // 1: direct-to-LDS kernel
   int32_t tile_n;        // output tile columns per right operand: 256, or 128 (SwiGLU, or a narrow plan)
+  int32_t tile_m;        // direct-load kernel: output tile rows, 256, or 128 (then tile_n is 128, or 64 for SwiGLU)
+  int32_t tail;          // direct-load kernel: some contracted block extent is no multiple of 32
   GemmTupleMeta* meta;   // direct-load kernel: per-tuple operand blocks (plan time)
   const int32_t* count;  // number of tuples of the join (plan time)
   float* partials;       // [slots][256 x 256] fp32 partial sums of split tiles
