@@ -17,6 +17,7 @@
 #include <mutex>
 #include <sstream>
 #include <string>
+#include <unordered_map>
 #include <vector>
 
 #include "ea_internal.h"
@@ -32,6 +33,7 @@ struct ea_relation {
   std::vector<int64_t> off;  // byte offset of every block
   int64_t nblocks = 0;
   int64_t nbytes = 0;
+  uint64_t layout = 0;  // equal for relations of one dtype, shape and partition, distinct otherwise
   void* data = nullptr;
   int64_t capacity = 0;
 };
@@ -368,6 +370,24 @@ void key_rel(std::ostringstream& k, const ea_relation* r) {
     for (int64_t s : r->splits[d]) k << s << ",";
     k << "]";
   }
+}
+
+// Layout ids: one per distinct (dtype, partition) a relation was created with.
+// The table grows with the distinct layouts of the process (a key of a few
+// numbers per split point), like the plan cache.
+uint64_t layout_id(const ea_relation* r) {
+  static std::mutex mu;
+  static auto* ids = new std::unordered_map<std::string, uint64_t>();  // intentionally leaked at exit
+  std::string k;
+  auto put = [&](const void* p, size_t n) { k.append(static_cast<const char*>(p), n); };
+  put(&r->dtype, sizeof(r->dtype));
+  for (int d = 0; d < r->rank; ++d) {  // every list starts at 0 and increases: the concatenation is unambiguous
+    put(r->splits[d].data(), r->splits[d].size() * sizeof(int64_t));
+  }
+  std::lock_guard<std::mutex> lk(mu);
+  auto it = ids->find(k);
+  if (it == ids->end()) it = ids->emplace(std::move(k), ids->size() + 1).first;
+  return it->second;
 }
 
 // Allocate a device buffer for a plan image and upload the image into it.
@@ -1706,11 +1726,85 @@ int prepare(const char* spec, int32_t join_op, int32_t agg_op, int32_t n_in, con
   return get_joinagg_plan(spec, *sp, join_op, agg_op, ops, prm, *oi, build, s, plan);
 }
 
-// Validate a run of a planned join-agg and find its plan (never building it).
-int lookup_run(const char* spec, int32_t join_op, int32_t agg_op, int32_t n_in, const ea_relation* const* in,
-               const ea_relation* out, const ea_params* params, hipStream_t s, OpInfo* oi, Plan** plan) {
+// Calls seen before: everything validation and planning look at (spec, ops,
+// operand layouts, parameters, device) maps to the resulting operation and
+// plan, so that a repeated call does neither again.  Only valid, planned calls
+// enter; data pointers are no part of it and are checked on every call.
+struct Call {
+  OpInfo oi;
+  Plan* plan = nullptr;
+};
+std::unordered_map<std::string, Call>& calls() {  // guarded by g_cache_mu
+  static auto* m = new std::unordered_map<std::string, Call>();  // intentionally leaked at exit
+  return *m;
+}
+constexpr size_t kMaxCalls = 65536;  // beyond it (ever-changing parameters) calls are validated in full
+
+template <class T>
+void put_raw(std::string* k, const T& v) {
+  k->append(reinterpret_cast<const char*>(&v), sizeof(T));
+}
+
+// The call's key, or an empty string for one to be validated in full (a
+// missing argument, or a sequence list too long to compare cheaply).
+std::string call_key(const char* spec, int32_t join_op, int32_t agg_op, int32_t n_in, const ea_relation* const* in,
+                     const ea_relation* out, const ea_params* prm, bool need_data, int dev) {
+  std::string k;
+  if (!spec || n_in < 1 || n_in > kMaxIn || !in || !out || (need_data && !out->data)) return k;
+  for (int i = 0; i < n_in; ++i)
+    if (!in[i] || (need_data && !in[i]->data)) return k;
+  if (prm && (prm->n_seq < 0 || prm->n_seq > 1024 || (prm->n_seq > 0 && !prm->seq_ends))) return k;
+  if (prm && prm->residual && !prm->residual->data) return k;
+  k.reserve(160 + (prm ? 8 * (size_t)prm->n_seq : 0));
+  k.append(spec);
+  k.push_back('\0');
+  put_raw(&k, dev);
+  put_raw(&k, join_op);
+  put_raw(&k, agg_op);
+  put_raw(&k, n_in);
+  for (int i = 0; i < n_in; ++i) put_raw(&k, in[i]->layout);
+  put_raw(&k, out->layout);
+  k.push_back(prm ? 1 : 0);
+  if (prm) {
+    put_raw(&k, prm->eps);
+    put_raw(&k, prm->scale);
+    put_raw(&k, prm->causal);
+    put_raw(&k, prm->store);
+    put_raw(&k, prm->gqa_group);
+    put_raw(&k, prm->residual ? prm->residual->layout : uint64_t(0));
+    for (int i = 0; i < prm->n_seq; ++i) put_raw(&k, prm->seq_ends[i]);
+  }
+  return k;
+}
+
+// Validate a join-agg call and find its plan; a missing plan is built when
+// `build` is set, else EA_ERR_NOPLAN.
+int find_call(const char* spec, int32_t join_op, int32_t agg_op, int32_t n_in, const ea_relation* const* in,
+              const ea_relation* out, const ea_params* params, bool need_data, bool build, hipStream_t s,
+              const Call** call) {
+  int dev = 0;
+  const bool have_dev = hipGetDevice(&dev) == hipSuccess;
+  const std::string key =
+      have_dev ? call_key(spec, join_op, agg_op, n_in, in, out, params, need_data, dev) : std::string();
+  if (!key.empty()) {
+    std::lock_guard<std::mutex> lk(g_cache_mu);
+    auto it = calls().find(key);
+    if (it != calls().end()) {
+      *call = &it->second;
+      return EA_OK;
+    }
+  }
+  thread_local Call slow;
   Spec sp;
-  return prepare(spec, join_op, agg_op, n_in, in, out, params, true, false, s, &sp, oi, plan);
+  slow.plan = nullptr;
+  int e = prepare(spec, join_op, agg_op, n_in, in, out, params, need_data, build, s, &sp, &slow.oi, &slow.plan);
+  if (e) return e;
+  *call = &slow;
+  if (!key.empty()) {
+    std::lock_guard<std::mutex> lk(g_cache_mu);
+    if (calls().size() < kMaxCalls) calls().emplace(key, slow);
+  }
+  return EA_OK;
 }
 
 // ---------------------------------------------------------------------------
@@ -1806,6 +1900,7 @@ int ea_relation_create(int32_t rank, const int64_t* shape, int32_t dtype, const 
     s += nblocks[d] + 1;
   }
   fill_layout(r.get());
+  r->layout = layout_id(r.get());
   if (data) {
     if ((uintptr_t)data % 256) return fail(EA_ERR_ARG, "relation data must be 256-byte aligned");
     if (capacity < r->nbytes)
@@ -2081,22 +2176,20 @@ int ea_joinagg_workspace(const char* spec, int32_t join_op, int32_t agg_op, int3
                          int64_t* ws_bytes, void* stream) {
   if (!ws_bytes) return fail(EA_ERR_ARG, "NULL ws_bytes");
   *ws_bytes = 0;
-  Spec sp;
-  OpInfo oi;
-  Plan* plan = nullptr;
-  int e = prepare(spec, join_op, agg_op, n_in, in, out, params, false, true, (hipStream_t)stream, &sp, &oi, &plan);
+  const Call* call = nullptr;
+  int e = find_call(spec, join_op, agg_op, n_in, in, out, params, false, true, (hipStream_t)stream, &call);
   if (e) return e;
-  *ws_bytes = plan->ws_bytes();
+  *ws_bytes = call->plan->ws_bytes();
   return ok();
 }
 
 int ea_joinagg(const char* spec, int32_t join_op, int32_t agg_op, int32_t n_in, const ea_relation* const* in,
                ea_relation* out, const ea_params* params, void* workspace, int64_t ws_bytes, void* stream) {
   hipStream_t s = (hipStream_t)stream;
-  OpInfo oi;
-  Plan* plan = nullptr;
-  int e = lookup_run(spec, join_op, agg_op, n_in, in, out, params, s, &oi, &plan);
+  const Call* call = nullptr;
+  int e = find_call(spec, join_op, agg_op, n_in, in, out, params, true, false, s, &call);
   if (e) return e;
+  const Plan* plan = call->plan;
   const int64_t need = plan->ws_bytes();
   if (need) {
     if (!workspace) return fail(EA_ERR_ARG, "this join-agg needs a workspace of %lld bytes", (long long)need);
@@ -2105,7 +2198,7 @@ int ea_joinagg(const char* spec, int32_t join_op, int32_t agg_op, int32_t n_in, 
       return fail(EA_ERR_CAPACITY, "workspace of %lld bytes below the %lld this join-agg needs", (long long)ws_bytes,
                   (long long)need);
   }
-  e = run_planned(plan, join_op, n_in, in, out, params, oi, need ? (char*)workspace : nullptr, s);
+  e = run_planned(plan, join_op, n_in, in, out, params, call->oi, need ? (char*)workspace : nullptr, s);
   if (e) return e;
   return ok();
 }
@@ -2113,10 +2206,10 @@ int ea_joinagg(const char* spec, int32_t join_op, int32_t agg_op, int32_t n_in, 
 int ea_joinagg_noalloc(const char* spec, int32_t join_op, int32_t agg_op, int32_t n_in, const ea_relation* const* in,
                        ea_relation* out, const ea_params* params, void* stream) {
   hipStream_t s = (hipStream_t)stream;
-  OpInfo oi;
-  Plan* plan = nullptr;
-  int e = lookup_run(spec, join_op, agg_op, n_in, in, out, params, s, &oi, &plan);
+  const Call* call = nullptr;
+  int e = find_call(spec, join_op, agg_op, n_in, in, out, params, true, false, s, &call);
   if (e) return e;
+  const Plan* plan = call->plan;
   const int64_t need = plan->ws_bytes();
   char* ws = nullptr;
   if (need) {
@@ -2133,7 +2226,7 @@ int ea_joinagg_noalloc(const char* spec, int32_t join_op, int32_t agg_op, int32_
       EA_HIP_TRY(hipGetLastError());
     }
   }
-  e = run_planned(plan, join_op, n_in, in, out, params, oi, ws, s);
+  e = run_planned(plan, join_op, n_in, in, out, params, call->oi, ws, s);
   if (e) return e;
   return ok();
 }
@@ -2166,11 +2259,9 @@ int check_repartition(const ea_relation* src, const ea_relation* dst, bool need_
 int get_repartition_plan(const ea_relation* src, const ea_relation* dst, bool build, hipStream_t s, Plan** out) {
   int dev = 0;
   EA_HIP_TRY(hipGetDevice(&dev));
-  std::ostringstream k;
-  k << "R|" << dev;
-  key_rel(k, src);
-  key_rel(k, dst);
-  const std::string key = k.str();
+  char kb[64];
+  snprintf(kb, sizeof(kb), "R|%d|%llu|%llu", dev, (unsigned long long)src->layout, (unsigned long long)dst->layout);
+  const std::string key = kb;
   Plan* plan = nullptr;
   {
     std::lock_guard<std::mutex> lk(g_cache_mu);
@@ -2331,6 +2422,7 @@ int64_t ea_plan_cache_size(void) {
 
 int ea_plan_cache_clear(void) {
   std::lock_guard<std::mutex> lk(g_cache_mu);
+  calls().clear();  // they point into the plans
   cache().clear();
   return ok();
 }

@@ -103,12 +103,22 @@ def _partition_args(partition):
     return nb, sp
 
 
-def _stream(stream) -> ctypes.c_void_p:
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_gpu_seen = False  # a GPU was available once (it stays so)
+
+
+def _stream(stream):
+    """The HIP stream handle of ``stream`` (default: torch's current one)."""
+    global _gpu_seen
     if stream is None:
-        if not torch.cuda.is_available():
-            return ctypes.c_void_p(None)  # host-side validation still runs; HIP calls then fail
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
+        if not _gpu_seen:
+            if not torch.cuda.is_available():
+                return None  # host-side validation still runs; HIP calls then fail
+            _gpu_seen = True
+        if _raw_stream is not None:  # the handle alone: torch's Stream object costs half a call
+            return _raw_stream(torch.cuda.current_device())
+        return torch.cuda.current_stream().cuda_stream
+    return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
 def version() -> int:
@@ -161,6 +171,7 @@ class Relation:
         _check(lib().ea_relation_create(len(self.shape), _arr(ctypes.c_int64, self.shape), DTYPES[dtype], nb, sp,
                                         ctypes.c_void_p(ptr) if ptr else None, cap, ctypes.byref(h)))
         self.handle = h
+        self._h = h.value  # the handle as a plain integer
 
     def __del__(self):
         h = getattr(self, "handle", None)
@@ -193,13 +204,20 @@ class Relation:
 
 def _params(eps=0.0, scale=0.0, causal=False, store=0, residual=None, gqa_group=0, seq_ends=None):
     """ea_params plus the host array it points at (kept alive by the caller)."""
-    ends = None
-    if seq_ends is not None:
-        ends = (ctypes.c_int64 * max(1, len(seq_ends)))(*[int(e) for e in seq_ends])
-    prm = _Params(eps, scale, int(causal), int(store), residual.handle.value if residual is not None else None,
-                  int(gqa_group), 0 if seq_ends is None else len(seq_ends),
-                  ctypes.cast(ends, ctypes.c_void_p) if ends is not None else None)
-    return prm, ends
+    res = residual.handle.value if residual is not None else None
+    if seq_ends is None:
+        return _Params(eps, scale, int(causal), int(store), res, int(gqa_group), 0, None), None
+    ends = (ctypes.c_int64 * max(1, len(seq_ends)))(*[int(e) for e in seq_ends])
+    return _Params(eps, scale, int(causal), int(store), res, int(gqa_group), len(seq_ends),
+                   ctypes.cast(ends, ctypes.c_void_p)), ends
+
+
+_HANDLES = [ctypes.c_void_p * max(n, 1) for n in range(9)]  # array types of the usual input counts
+
+
+def _handles(inputs):
+    n = len(inputs)
+    return (_HANDLES[n] if n < len(_HANDLES) else ctypes.c_void_p * n)(*[r._h for r in inputs])
 
 
 def new_workspace(nbytes: int, device=None) -> torch.Tensor:
@@ -212,11 +230,11 @@ _WS = {}  # (device, stream handle) -> workspace tensor of the calls on that str
 _WS_RETIRED = []  # outgrown workspaces: kernels queued earlier may still use them
 
 
-def _stream_workspace(nbytes: int, stream: ctypes.c_void_p) -> torch.Tensor:
+def _stream_workspace(nbytes: int, stream) -> torch.Tensor:
     """The binding's workspace for calls on ``stream``: calls on one stream run
     in order, so they share one buffer, grown (zeroed) when a plan needs more."""
     dev = torch.cuda.current_device()
-    key = (dev, stream.value or 0)
+    key = (dev, stream or 0)
     buf = _WS.get(key)
     if buf is None or buf.numel() < nbytes:
         if buf is not None:
@@ -232,7 +250,7 @@ def joinagg_workspace(spec: str, join_op: int, agg_op: int, inputs: Sequence[Rel
                       store: int = 0, gqa_group: int = 0, seq_ends=None, stream=None) -> int:
     """Plan a join-agg configuration (first call: allocate the plan, run the
     GPU join, wait for it) and return the workspace bytes its runs need."""
-    handles = _arr(ctypes.c_void_p, [r.handle.value for r in inputs])
+    handles = _handles(inputs)
     prm, _ends = _params(eps, scale, causal, store, residual, gqa_group, seq_ends)
     n = ctypes.c_int64()
     _check(lib().ea_joinagg_workspace(spec.encode(), join_op, agg_op, len(inputs), handles, out.handle,
@@ -253,19 +271,29 @@ def joinagg(spec: str, join_op: int, agg_op: int, inputs: Sequence[Relation], ou
     joinagg_workspace).  ``workspace``: a device buffer from new_workspace
     for key-split partials; by default one buffer per stream, held by the
     binding."""
-    handles = _arr(ctypes.c_void_p, [r.handle.value for r in inputs])
+    handles = _handles(inputs)
     prm, _ends = _params(eps, scale, causal, store, residual, gqa_group, seq_ends)
     s = _stream(stream)
+    spec_b, prm_p, n_in = spec.encode(), ctypes.byref(prm), len(inputs)
+    # A planned configuration whose workspace fits runs at once; otherwise it
+    # is planned first and the workspace grown.  Any other failure comes again
+    # from the planning call or the second run.
+    buf = workspace
+    if buf is None and _WS:
+        buf = _WS.get((torch.cuda.current_device(), s or 0))
+    if buf is None:
+        ws, nbytes = None, 0
+    else:
+        ws, nbytes = buf.data_ptr(), buf.numel() * buf.element_size()
+    if lib().ea_joinagg(spec_b, join_op, agg_op, n_in, handles, out._h, prm_p, ws, nbytes, s) == OK:
+        return
     need = ctypes.c_int64()
-    spec_b = spec.encode()
-    _check(lib().ea_joinagg_workspace(spec_b, join_op, agg_op, len(inputs), handles, out.handle, ctypes.byref(prm),
-                                      ctypes.byref(need), s))
+    _check(lib().ea_joinagg_workspace(spec_b, join_op, agg_op, n_in, handles, out._h, prm_p, ctypes.byref(need), s))
     ws, nbytes = None, 0
     if need.value:
         buf = workspace if workspace is not None else _stream_workspace(need.value, s)
-        ws, nbytes = ctypes.c_void_p(buf.data_ptr()), buf.numel() * buf.element_size()
-    _check(lib().ea_joinagg(spec_b, join_op, agg_op, len(inputs), handles, out.handle, ctypes.byref(prm), ws, nbytes,
-                            s))
+        ws, nbytes = buf.data_ptr(), buf.numel() * buf.element_size()
+    _check(lib().ea_joinagg(spec_b, join_op, agg_op, n_in, handles, out._h, prm_p, ws, nbytes, s))
 
 
 def joinagg_noalloc(spec: str, join_op: int, agg_op: int, inputs: Sequence[Relation], out: Relation, *,
@@ -274,7 +302,7 @@ def joinagg_noalloc(spec: str, join_op: int, agg_op: int, inputs: Sequence[Relat
     """ea_joinagg_noalloc: run a join-agg planned earlier (joinagg_workspace)
     with the library's own per-device workspace array; allocates nothing.
     Calls that may overlap in time on one GPU race on that array."""
-    handles = _arr(ctypes.c_void_p, [r.handle.value for r in inputs])
+    handles = _handles(inputs)
     prm, _ends = _params(eps, scale, causal, store, residual, gqa_group, seq_ends)
     _check(lib().ea_joinagg_noalloc(spec.encode(), join_op, agg_op, len(inputs), handles, out.handle,
                                     ctypes.byref(prm), _stream(stream)))
@@ -290,14 +318,16 @@ def repartition(src: Relation, dst: Relation, stream=None, *, store: int = 0) ->
     """Write ``src``'s dense tensor into ``dst`` under ``dst``'s partition
     (``store`` as for joinagg); planned on first use."""
     s = _stream(stream)
-    _check(lib().ea_repartition_plan(src.handle, dst.handle, s))
-    _check(lib().ea_repartition_ex(src.handle, dst.handle, int(store), s))
+    if lib().ea_repartition_ex(src._h, dst._h, int(store), s) == OK:
+        return
+    _check(lib().ea_repartition_plan(src._h, dst._h, s))
+    _check(lib().ea_repartition_ex(src._h, dst._h, int(store), s))
 
 
 def join_tuples(spec: str, join_op: int, inputs: Sequence[Relation], out: Relation, *, causal: bool = False,
                 scale: float = 1.0, eps: float = 1e-6, gqa_group: int = 0, seq_ends=None, stream=None):
     """The GPU-built tuple table and CSR group offsets of a join (synchronous)."""
-    handles = _arr(ctypes.c_void_p, [r.handle.value for r in inputs])
+    handles = _handles(inputs)
     prm, _ends = _params(eps, scale, causal, 0, None, gqa_group, seq_ends)
     n_t, n_g = ctypes.c_int64(), ctypes.c_int64()
     dev = out.data.device if out.data is not None else torch.device("cuda")
