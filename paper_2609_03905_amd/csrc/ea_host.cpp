@@ -295,7 +295,7 @@ struct Image {
   size_t put_vec(const std::vector<T>& v) { return put(v.data(), v.size() * sizeof(T)); }
 };
 
-enum Kind { K_GENERIC = 1, K_GEMM, K_CONTRACT, K_RMSNORM, K_SOFTMAX, K_ATTENTION, K_REPART };
+enum Kind { K_GENERIC = 1, K_GEMM, K_CONTRACT, K_REDUCE, K_RMSNORM, K_SOFTMAX, K_ATTENTION, K_REPART };
 
 // row-reduction plan constants (see RowArgs)
 struct RowLayout {
@@ -329,6 +329,7 @@ struct Plan {
   bool gemm_tail = false;    // some contracted block extent is no multiple of 32
   GemmTupleMeta* d_gemm_meta = nullptr;  // direct-load plans: per-tuple operand blocks
   // contraction: everything of its arguments but the data pointers
+  ReduceArgs red;
   ContractArgs con;
   int con_a = 0;  // input that is the kernel's A
   // repartition: tasks of kRepTaskBytesSmall (relations below kRepLargeBytes)
@@ -421,6 +422,7 @@ struct OpInfo {
   char gh = 0, gg = 0;           // query-head and key/value-head letters (gqa > 1)
   int head_dim = -1;             // their dim in Q and in K/V
   ContractDims con{};            // letters of a two-operand contraction (dims only)
+  ReduceDims red{};              // letters of a reduction or elementwise join (dims only)
   std::vector<int64_t> seq_ends; // packed sequences along cq/ck (attention), empty: one
 };
 
@@ -577,6 +579,40 @@ bool contraction_ok(const Spec& sp, const ea_relation* const* ops, ContractDims*
   return work <= kConMaxWork;
 }
 
+// An einsum that the reduction kernel takes: one or two inputs of one dtype, at
+// most one contracted letter and kRedRank output letters, 32-bit byte offsets
+// inside blocks, and a bounded table of tuples.
+constexpr int64_t kRedMaxTuples = int64_t(1) << 22;
+bool reduction_ok(const Spec& sp, const ea_relation* const* ops, ReduceDims* d) {
+  const int out = sp.n_in;
+  if (sp.n_in > 2 || sp.rank[out] > kRedRank || (sp.n_in == 2 && ops[0]->dtype != ops[1]->dtype)) return false;
+  memset(d, 0, sizeof(*d));
+  d->n_in = sp.n_in;
+  d->out_rank = sp.rank[out];
+  for (int o = 0; o <= out; ++o)
+    if (max_block_bytes(ops[o]) >= INT32_MAX) return false;
+  char contracted = 0;
+  int64_t tuples = 1;
+  for (int x = 0; x < sp.rank[out]; ++x) tuples *= ops[out]->nb[x];
+  for (int i = 0; i < sp.n_in; ++i) {
+    d->rank[i] = sp.rank[i];
+    d->cd[i] = -1;
+    for (int x = 0; x < kRedRank; ++x) {
+      const int y = x - (kRedRank - sp.rank[out]);
+      d->od[i][x] = y >= 0 ? find_dim(sp, i, sp.let[out][y]) : -1;
+    }
+    for (int x = 0; x < sp.rank[i]; ++x) {
+      const char l = sp.let[i][x];
+      if (find_dim(sp, out, l) >= 0) continue;
+      if (contracted && contracted != l) return false;
+      if (!contracted) tuples *= ops[i]->nb[x];
+      contracted = l;
+      d->cd[i] = x;
+    }
+  }
+  return tuples <= kRedMaxTuples;
+}
+
 bool is_float_dtype(int32_t dt) { return dt == EA_F32 || dt == EA_BF16 || dt == EA_F16; }
 
 int classify(const Spec& sp, int32_t join_op, int32_t agg_op, const ea_relation* const* ops,
@@ -633,6 +669,7 @@ int classify(const Spec& sp, int32_t join_op, int32_t agg_op, const ea_relation*
         }
       }
       if (join_op == EA_JOIN_MUL && agg_op == EA_AGG_SUM && contraction_ok(sp, ops, &oi->con)) oi->kind = K_CONTRACT;
+      else if (reduction_ok(sp, ops, &oi->red)) oi->kind = K_REDUCE;
       return EA_OK;
     }
     case EA_OP_SWIGLU: {
@@ -1282,6 +1319,61 @@ GemmDlPlan gemm_units_mid(const ea_relation* a, const ea_relation* c, int tn) {
   return out;
 }
 
+int build_reduce(const ea_relation* const* ops, int n_in, int32_t join_op, int32_t agg_op, const ReduceDims& d,
+                 int64_t tuple_cap, Image* img, Extra* ex, ReduceArgs* a) {
+  const ea_relation* C = ops[n_in];
+  memset(a, 0, sizeof(*a));
+  a->n_in = n_in;
+  a->join = join_op;
+  a->agg = agg_op;
+  a->dt_in = ops[0]->dtype;
+  a->dt_out = C->dtype;
+  int64_t outputs = 1, len = 1;
+  for (int x = 0; x < C->rank; ++x) outputs *= C->shape[x];
+  a->nt = 1;
+  bool along = false;  // the contracted letter is the contiguous one of every input that has it
+  for (int i = 0; i < n_in; ++i) {
+    if (d.cd[i] < 0) continue;
+    const bool last = d.cd[i] == ops[i]->rank - 1;
+    along = len == 1 ? last : along && last;
+    len = std::max<int64_t>(ops[i]->shape[d.cd[i]], 2);
+    a->nt = ops[i]->nb[d.cd[i]];
+  }
+  // Lanes along a contiguous contracted letter, unless it is so short that
+  // most would idle.  Four wavefronts per output while one each leaves CUs
+  // idle; otherwise lanes along the output, and as many wavefronts per 64
+  // elements as it takes to have about 2000 of them, each with at least 8 terms.
+  a->rows = along && len >= 32;
+  a->rounds = 1;
+  a->threads = 256;
+  if (a->rows) {
+    a->R = outputs < 4096 && len >= 256 ? 4 : 1;
+  } else {
+    a->R = outputs >= 131072 || len < 32 ? 1 : outputs >= 32768 || len < 128 ? 4 : 16;
+    if (a->R == 16) a->threads = 1024;
+    if (a->R == 1 && outputs >= (int64_t(1) << 20)) a->rounds = 4;  // fewer, longer workgroups
+  }
+  const int64_t per = a->threads / 64 / a->R * (a->rows ? 1 : 64) * a->rounds;
+  std::vector<RedWork> work;
+  for (int64_t b = 0; b < C->nblocks; ++b) {
+    int64_t n = 1;
+    int32_t co[kMaxRank];
+    block_coords(C, b, co);
+    for (int x = 0; x < C->rank; ++x) n *= C->splits[x][co[x] + 1] - C->splits[x][co[x]];
+    for (int64_t s = 0; s < n; s += per) {
+      RedWork w;
+      memset(&w, 0, sizeof(w));
+      w.block = (int32_t)b;
+      w.start = (int32_t)s;
+      work.push_back(w);
+    }
+  }
+  ex->work = img->put_vec(work);
+  ex->n_work = (int64_t)work.size();
+  ex->meta = img->put_zero((size_t)tuple_cap * sizeof(RedMeta));
+  return EA_OK;
+}
+
 int build_rows(const Spec& sp, const ea_relation* const* ops, const OpInfo& oi, Image* img, Extra* ex,
                RowLayout* lay) {
   // rows of a group: points of the group letters' box; every group has the
@@ -1497,7 +1589,7 @@ int get_joinagg_plan(const char* spec_str, const Spec& sp, int32_t join_op, int3
   for (int64_t e : oi.seq_ends) k << e << ",";
   for (int o = 0; o <= sp.n_in; ++o) key_rel(k, ops[o]);
   const ea_relation* res = prm ? prm->residual : nullptr;
-  if (res && (oi.kind == K_GEMM || oi.kind == K_GENERIC || oi.kind == K_CONTRACT)) k << "|res" << res->dtype;
+  if (res && (oi.kind == K_GEMM || oi.kind == K_GENERIC || oi.kind == K_CONTRACT || oi.kind == K_REDUCE)) k << "|res" << res->dtype;
   const std::string key = k.str();
   std::lock_guard<std::mutex> lk(g_cache_mu);
   auto it = cache().find(key);
@@ -1584,6 +1676,7 @@ int get_joinagg_plan(const char* spec_str, const Spec& sp, int32_t join_op, int3
       p->ws_partial_bytes = slots * slot_bytes;
       break;
     }
+    case K_REDUCE: e = build_reduce(ops, sp.n_in, join_op, agg_op, oi.red, p->tuple_cap, &img, &ex, &p->red); break;
     case K_CONTRACT: e = build_contract(ops, oi.con, p->tuple_cap, &img, &ex, &p->con); break;
     case K_RMSNORM:
     case K_SOFTMAX: e = build_rows(sp, ops, oi, &img, &ex, &p->rows); break;
@@ -1615,6 +1708,18 @@ int get_joinagg_plan(const char* spec_str, const Spec& sp, int32_t join_op, int3
     a.n_units = (int32_t)p->n_work;
     a.meta = p->d_gemm_meta;
     EA_HIP_TRY(launch_gemm_prep(a, (GemmUnit*)(p->dmem + ex.work), p->tuple_cap, s));
+    EA_HIP_TRY(hipStreamSynchronize(s));
+  }
+  if (oi.kind == K_REDUCE) {  // the join and the block tables resolved into the work list
+    p->red.n_work = p->n_work;
+    p->red.work = (const RedWork*)(p->dmem + ex.work);
+    p->red.meta = (const RedMeta*)(p->dmem + ex.meta);
+    ReduceDims d = oi.red;
+    d.tuples = p->d_tuples;
+    d.goff = p->d_goff;
+    for (int o = 0; o <= sp.n_in; ++o) d.blk[o] = p->d_blk[o];
+    EA_HIP_TRY(launch_reduce_prep(d, (RedMeta*)(p->dmem + ex.meta), (RedWork*)(p->dmem + ex.work), p->n_work,
+                                  p->d_count, p->tuple_cap, s));
     EA_HIP_TRY(hipStreamSynchronize(s));
   }
   if (oi.kind == K_CONTRACT) {  // the join and the block tables resolved into the work list
@@ -2084,6 +2189,14 @@ int run_planned(const Plan* plan, int32_t join_op, int32_t n_in, const ea_relati
       a.partials = (float*)(ws + kWsCounterBytes);
       a.counters = (int32_t*)ws;
       EA_HIP_TRY(launch_gemm(a, s));
+      break;
+    }
+    case K_REDUCE: {
+      ReduceArgs a = plan->red;
+      for (int i = 0; i < n_in; ++i) a.in[i] = (const char*)in[i]->data;
+      a.out = (char*)out->data;
+      a.res = res ? (const char*)res->data : nullptr;
+      EA_HIP_TRY(launch_reduce(a, s));
       break;
     }
     case K_CONTRACT: {

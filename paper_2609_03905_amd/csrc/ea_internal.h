@@ -116,6 +116,50 @@ struct GenArgs {
 hipError_t launch_generic(const GenArgs& a, hipStream_t s);
 
 // ---------------------------------------------------------------------------
+// Einsums of one or two inputs of one dtype, at most one contracted letter and
+// kRedRank output letters: reductions, elementwise joins, transposes.
+// ---------------------------------------------------------------------------
+constexpr int kRedRank = 4;
+struct RedMeta {            // one tuple (plan time)
+  int64_t off[2];           // input block byte offsets
+  int32_t os[2][kRedRank];  // element strides of the output letters (right-aligned; 0: absent)
+  int32_t cs[2];            // and of the contracted letter
+  int32_t cext;             // its extent (1: none)
+  int32_t pad;
+};
+static_assert(sizeof(RedMeta) == 64, "RedMeta layout");
+struct RedWork {      // one workgroup: consecutive elements of one output block
+  int64_t ooff;       // the fields but block and start are filled at plan time
+  int32_t block, start;
+  int32_t gb, n;      // the group's first tuple; elements of the block
+  int32_t ext[kRedRank];
+};
+struct ReduceArgs {
+  const RedWork* work;
+  const RedMeta* meta;
+  const char* in[2];
+  char* out;
+  const char* res;    // residual (layout and dtype of out) or null
+  int64_t n_work;
+  int32_t n_in, join, agg, dt_in, dt_out;
+  int32_t nt;         // tuples of a group
+  int32_t R;          // wavefronts per output (rows) or per 64 outputs
+  int32_t rounds;     // outputs per thread
+  int32_t threads, rows;
+};
+struct ReduceDims {   // dims of the letters in each operand (-1: absent)
+  const int32_t* tuples;
+  const int32_t* goff;
+  const DevBlk* blk[3];  // inputs, then output
+  int32_t n_in, out_rank;
+  int32_t rank[2];
+  int32_t od[2][kRedRank], cd[2];
+};
+hipError_t launch_reduce(const ReduceArgs& a, hipStream_t s);
+hipError_t launch_reduce_prep(const ReduceDims& d, RedMeta* meta, RedWork* work, int64_t n_work, const int32_t* count,
+                              int64_t tuple_cap, hipStream_t s);
+
+// ---------------------------------------------------------------------------
 // Repartition: the overlay of the source and destination partitions cuts the
 // tensor into boxes, each inside exactly one source block and one destination
 // block; a task copies a range of a box's rows (rows run along the last dim).
