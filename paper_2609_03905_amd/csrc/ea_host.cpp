@@ -299,7 +299,7 @@ enum Kind { K_GENERIC = 1, K_GEMM, K_CONTRACT, K_REDUCE, K_RMSNORM, K_SOFTMAX, K
 
 // row-reduction plan constants (see RowArgs)
 struct RowLayout {
-  int32_t row_len = 0, vec = 0, cps = 0, affine = 0, seg_len = 0, nseg = 0;
+  int32_t row_len = 0, vec = 0, cps = 0, affine = 0, seg_len = 0, nseg = 0, seg_elems = 0;
   int64_t xs = 0, ys = 0, ws = 0, wbase = 0;
 };
 
@@ -1395,6 +1395,11 @@ int build_rows(const Spec& sp, const ea_relation* const* ops, const OpInfo& oi, 
     even &= b + 1 < x->nb[dl] ? n == first : n <= first;
   }
   lay->cps = even ? (int32_t)first : 0;
+  lay->seg_elems = (int32_t)(x->splits[dl][1] - x->splits[dl][0]);
+  for (int b = 0; b < x->nb[dl]; ++b) {
+    const int64_t n = x->splits[dl][b + 1] - x->splits[dl][b];
+    if (b + 1 < x->nb[dl] ? n != x->splits[dl][1] : n > x->splits[dl][1]) lay->seg_elems = 0;
+  }
   // affine layout: equal segments, x and y with one partition (w along the
   // normalised letter too), and block offsets at fixed strides along it
   const int nseg = x->nb[dl];
@@ -2235,6 +2240,9 @@ int run_planned(const Plan* plan, int32_t join_op, int32_t n_in, const ea_relati
       a.vec = plan->rows.vec;
       a.seg_chunks = plan->rows.cps;
       a.seg_inv = a.seg_chunks > 0 ? 1.0f / (float)a.seg_chunks : 0.0f;
+      a.max_seg = plan->rows.nseg;
+      a.seg_elems = plan->rows.seg_elems;
+      a.seg_elems_inv = a.seg_elems > 0 ? 1.0f / (float)a.seg_elems : 0.0f;
       a.affine = plan->rows.affine;
       a.stream_out = params ? params->store : 0;
       a.seg_len = plan->rows.seg_len;

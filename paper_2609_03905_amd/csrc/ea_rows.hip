@@ -13,8 +13,9 @@
 // shared by two wavefronts, whose partial sums of squares meet in LDS.
 //
 // Causal softmax skips the loads of keys after the row's query position and
-// stores zeros there.  Rows too long for registers, or segments that are not
-// 16-byte multiples, take a scalar path that re-reads the row.
+// stores zeros there.  Segments that are not 16-byte multiples take an element
+// path that also holds the row in registers; rows too long for registers a
+// scalar path that re-reads the row.
 #include <type_traits>
 
 #include "ea_device.h"
@@ -26,6 +27,7 @@ namespace {
 constexpr int kThreads = 64 * kRowsPerTask;  // one row per wavefront
 constexpr int kMaxSeg = 64;    // segments per row on the register path
 constexpr int kMaxK = 16;      // 16-byte chunks per lane on the register path
+constexpr int kMaxElems = 16384;  // row elements on the element path
 
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 
@@ -44,8 +46,8 @@ struct RowInfo {
   int32_t qpos;    // query position of the row (softmax causal)
 };
 
-__device__ __forceinline__ RowInfo row_info(const RowArgs& a, int task_row) {
-  const RowTask& task = a.tasks[blockIdx.x];
+__device__ __forceinline__ RowInfo row_info(const RowArgs& a, int task_index, int task_row) {
+  const RowTask& task = a.tasks[task_index];
   RowInfo ri;
   const int g = task.g;
   ri.row = task.row0 + task_row;
@@ -155,7 +157,7 @@ __global__ __launch_bounds__(kThreads * WPR) void rows_vec_kernel(RowArgs a) {
     yrow = ld_uniform(&task.yrow) + (int64_t)wrow * a.seg_len * esy;
     if (SOFTMAX && a.causal) qpos = ld_uniform(&task.qlo) + row % ld_uniform(&task.qext);
   } else {
-    ri = row_info(a, wid);  // every row of the task is in the same group
+    ri = row_info(a, blockIdx.x, wid);  // every row of the task is in the same group
     total = fill_segments(a, ri, st, lane, ES);
     nseg = ri.nseg;
     qpos = ri.qpos;
@@ -439,13 +441,164 @@ __global__ __launch_bounds__(kThreads * WPR) void rows_vec_kernel(RowArgs a) {
 }
 
 // ---------------------------------------------------------------------------
+// element path: rows or segments that are no multiples of 16 bytes, up to
+// kMaxElems elements.  W wavefronts share a row and hold it in registers, K
+// elements per lane (loaded one by one, lanes along the row), so that the row
+// is read once, all of it in flight at once, where the scalar path below reads
+// it two or three times with one load in flight per lane.  One wavefront per
+// row (four rows per workgroup) up to 512 elements, four up to 8192 (8, 16 or
+// 32 elements per lane), sixteen beyond.  Sixteen wavefronts already above 2048
+// keep only two rows per CU in flight, each waiting for its table, its loads
+// and its barriers in turn (causal softmax 4 x 3092^2 bf16: 108 us against 54);
+// 64 elements per lane on one wavefront: 95 us.
+// Times, scalar path -> this: RMSNorm 1089 x 7041 f32 102 -> 21 us, 211 x 653
+// bf16 7.2 -> 4.5; causal softmax 4 x 3092^2 bf16 124 -> 54 us, softmax 2893^2
+// f32 68 -> 16 us.  Bound by its 2- and 4-byte accesses and the row's latency.
+// ---------------------------------------------------------------------------
+struct ElemSegs {
+  int32_t start[kMaxSeg + 1];  // first element of the segment within the row
+  int64_t x[kMaxSeg], y[kMaxSeg], w[kMaxSeg];  // byte offsets of the row's segment (w: the weight block)
+};
+
+template <typename XT, bool SOFTMAX, int K, int W>
+__global__ __launch_bounds__(W == 1 ? kThreads : 64 * W) void rows_elem_kernel(RowArgs a) {
+  constexpr int RPB = W == 1 ? kRowsPerTask : 1;  // rows per workgroup
+  constexpr int ES = sizeof(XT);
+  __shared__ ElemSegs tabs[RPB];
+  __shared__ float s_red[W];
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  const int task = W == 1 ? blockIdx.x : blockIdx.x / kRowsPerTask;
+  const int trow = W == 1 ? wid : blockIdx.x % kRowsPerTask;
+  if (trow >= a.tasks[task].nrows) return;  // a whole wavefront (W == 1) or workgroup
+  const RowInfo ri = row_info(a, task, trow);
+  const int d_last = a.rank - 1, esy = a.dt_y == EA_F32 ? 4 : 2;
+  ElemSegs& st = tabs[W == 1 ? wid : 0];
+  if (W == 1 || wid == 0) {  // lane s describes segment s
+    int len = 0;
+    if (lane < ri.nseg) {
+      const int32_t* tp = a.tuples + (int64_t)(ri.t0 + lane) * a.tuple_stride;
+      const DevBlk& xb = a.blk_x[tp[1]];
+      len = xb.ext[d_last];
+      st.start[lane] = xb.lo[d_last];  // segments tile the row: its position is its first element
+      st.x[lane] = xb.off + (int64_t)ri.row * len * ES;
+      st.y[lane] = a.blk_y[tp[0]].off + (int64_t)ri.row * len * esy;
+      st.w[lane] = a.blk_w ? a.blk_w[tp[2]].off : 0;
+    }
+  }
+  if constexpr (W == 1) {
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  } else {
+    __syncthreads();
+  }
+  const int n = a.row_len, nseg = ri.nseg, e0 = W == 1 ? lane : threadIdx.x;
+  const int seen = SOFTMAX && a.causal ? min(n, ri.qpos + 1) : n;  // visible elements
+  // segment of element e: floor((e + 1/2) / length) where all but the last are
+  // of one length (exact in fp32 for e below 2^14, see rows_vec_kernel), else a
+  // binary search
+  auto seg_of_elem = [&](int e) {
+    if (a.seg_elems > 0) return min((int)(((float)e + 0.5f) * a.seg_elems_inv), nseg - 1);
+    int lo = 0, hi = nseg;
+    while (hi - lo > 1) {
+      const int m = (lo + hi) >> 1;
+      if (st.start[m] <= e) lo = m;
+      else hi = m;
+    }
+    return lo;
+  };
+  float f[K];
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const int e = e0 + k * 64 * W;
+    f[k] = 0.0f;
+    if (e < seen) {
+      const int sg = seg_of_elem(e);
+      const XT* xp = reinterpret_cast<const XT*>(a.x + st.x[sg]) + (e - st.start[sg]);
+      if constexpr (ES == 2) f[k] = bf16_to_f32(*xp);
+      else f[k] = *xp;
+    }
+  }
+  // a wavefront's value combined over the row's wavefronts, in their order
+  auto across = [&](float v, auto op) {
+    if constexpr (W > 1) {
+      __syncthreads();
+      if (lane == 0) s_red[wid] = v;
+      __syncthreads();
+      v = s_red[0];
+#pragma unroll
+      for (int q = 1; q < W; ++q) v = op(v, s_red[q]);
+    }
+    return v;
+  };
+  auto plus = [](float x, float y) { return x + y; };
+  float scale;
+  if constexpr (SOFTMAX) {
+    float m = -INFINITY;
+#pragma unroll
+    for (int k = 0; k < K; ++k) m = e0 + k * 64 * W < seen ? fmaxf(m, f[k]) : m;
+    m = across(wave_max(m), [](float x, float y) { return fmaxf(x, y); });
+    float l = 0.0f;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      f[k] = e0 + k * 64 * W < seen ? __expf(f[k] - m) : 0.0f;
+      l += f[k];
+    }
+    l = across(wave_sum(l), plus);
+    scale = m == -INFINITY ? 0.0f : 1.0f / l;
+    if (m == -INFINITY) {  // every visible entry -inf: zeros (the terms above are NaN)
+#pragma unroll
+      for (int k = 0; k < K; ++k) f[k] = 0.0f;
+    }
+  } else {
+    float ss = 0.0f;
+#pragma unroll
+    for (int k = 0; k < K; ++k) ss += f[k] * f[k];
+    ss = across(wave_sum(ss), plus);
+    scale = 1.0f / sqrtf(ss / (float)n + a.eps);
+  }
+  auto write_row = [&](auto stream_tag) {
+    constexpr bool STREAM = decltype(stream_tag)::value;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const int e = e0 + k * 64 * W;
+      if (e >= n) continue;
+      const int sg = seg_of_elem(e), i = e - st.start[sg];
+      float o = f[k] * scale;
+      if constexpr (!SOFTMAX) o = ld_elem(a.w + st.w[sg], i, a.dt_w) * o;
+      char* yp = a.y + st.y[sg] + (int64_t)i * esy;
+      if (esy == 4) store_out<STREAM>(yp, __float_as_uint(o));
+      else store_out<STREAM>(yp, a.dt_y == EA_BF16 ? f32_to_bf16(o) : f32_to_f16(o));
+    }
+  };
+  if (a.stream_out) write_row(std::true_type{});
+  else write_row(std::false_type{});
+}
+
+template <typename XT, bool SOFTMAX, int K, int W>
+void launch_elem_kw(const RowArgs& a, hipStream_t s) {
+  const uint32_t tasks = (uint32_t)a.n_rowtasks;
+  hipLaunchKernelGGL((rows_elem_kernel<XT, SOFTMAX, K, W>), dim3(W == 1 ? tasks : tasks * kRowsPerTask),
+                     dim3(W == 1 ? kThreads : 64 * W), 0, s, a);
+}
+template <typename XT, bool SOFTMAX>
+void launch_elem(const RowArgs& a, hipStream_t s) {
+  const int L = a.row_len;
+  if (L <= 512) launch_elem_kw<XT, SOFTMAX, 8, 1>(a, s);
+  else if (L <= 2048) launch_elem_kw<XT, SOFTMAX, 8, 4>(a, s);
+  else if (L <= 4096) launch_elem_kw<XT, SOFTMAX, 16, 4>(a, s);
+  else if (L <= 8192) launch_elem_kw<XT, SOFTMAX, 32, 4>(a, s);
+  else launch_elem_kw<XT, SOFTMAX, 16, 16>(a, s);
+}
+
+// ---------------------------------------------------------------------------
 // scalar path: any segment lengths, any row length; re-reads the row
 // ---------------------------------------------------------------------------
 template <bool SOFTMAX>
 __global__ __launch_bounds__(kThreads) void rows_scalar_kernel(RowArgs a) {
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   if (wid >= a.tasks[blockIdx.x].nrows) return;
-  const RowInfo ri = row_info(a, wid);
+  const RowInfo ri = row_info(a, blockIdx.x, wid);
   const int d_last = a.rank - 1;
   auto visit = [&](auto&& fn) {
     for (int s = 0; s < ri.nseg; ++s) {
@@ -516,6 +669,9 @@ hipError_t launch_rows(const RowArgs& a, hipStream_t s) {
     const int64_t chunks = (int64_t)a.row_len * (a.dt_x == EA_BF16 ? 2 : 4) / 16;
     if (a.dt_x == EA_BF16) launch_vec_k<uint16_t, SOFTMAX>(a, chunks, grid, block, s);
     else launch_vec_k<float, SOFTMAX>(a, chunks, grid, block, s);
+  } else if (a.max_seg <= kMaxSeg && a.row_len <= kMaxElems) {
+    if (a.dt_x == EA_BF16) launch_elem<uint16_t, SOFTMAX>(a, s);
+    else launch_elem<float, SOFTMAX>(a, s);
   } else {
     hipLaunchKernelGGL((rows_scalar_kernel<SOFTMAX>), grid, block, 0, s, a);
   }

@@ -1,0 +1,64 @@
+"""RMSNorm and softmax over rows that no 16-byte vector divides: every share of
+wavefronts per row, even and uneven segments, masks and infinities, against the
+oracle.
+
+Tolerance: f32 rows as the fp32 path's other tests (1e-5: sums of at most 17000
+fp32 terms in parallel partial sums); bf16 outputs against the rounded oracle.
+"""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+from helpers import assert_close, empty, expected, upload, values
+from paper_2609_03905_amd import ea
+
+pytestmark = pytest.mark.gpu
+
+LENGTHS = [1, 7, 63, 511, 513, 2047, 2049, 4095, 4099, 8191, 8193, 16383, 16387]  # the last: the scalar path
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("n", LENGTHS)
+def test_rmsnorm_row_lengths(n, dtype):
+    rows = 6  # one and a half row tasks
+    x, w = synth.normal((rows, n), 3, dtype=dtype), synth.uniform((n,), 4, 0.5, 1.5, dtype=dtype)
+    part = synth.splits(n, 1000) if n % 2 else synth.random_splits(n, 5, np.random.default_rng(1))
+    X, W = upload(x, dtype, [[0, rows], part]), upload(w, dtype, [part])
+    for store in (ea.STORE_CACHED, ea.STORE_STREAM):
+        Y = empty((rows, n), dtype, [[0, rows], part])
+        ea.joinagg("tc,c->tc", ea.OP_RMSNORM, ea.AGG_SUM, [X, W], Y, eps=1e-6, store=store)
+        ref = oracle.rmsnorm(synth.to_f64(x, dtype), synth.to_f64(w, dtype), 1e-6)
+        assert_close(values(Y), expected(ref, dtype), rel_fro=1e-5 if dtype == "f32" else 1e-3, what=f"rmsnorm {n}")
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("n,uneven", [(1, False), (63, True), (511, False), (700, True), (2051, False), (4101, True)])
+def test_softmax_row_lengths(n, uneven, causal):
+    rng = np.random.default_rng(2)
+    pk = synth.random_splits(n, 7, rng) if uneven else synth.splits(n, 500)
+    pq = synth.random_splits(n, 3, rng)
+    s = synth.normal((1, n, n), 5, 2.0, dtype="f32")
+    S, P = upload(s, "f32", [[0, 1], pq, pk]), empty((1, n, n), "f32", [[0, 1], pq, pk])
+    ea.joinagg("hqk->hqk", ea.OP_SOFTMAX, ea.AGG_LSE, [S], P, causal=causal)
+    got, x = values(P)[0], synth.to_f64(s, "f32")[0]
+    if causal:
+        x = np.where(np.tri(n, dtype=bool), x, -np.inf)
+    e = np.exp(x - x.max(1, keepdims=True))
+    assert_close(got, e / e.sum(1, keepdims=True), rel_fro=1e-5, what=f"softmax {n} causal={causal}")
+    if causal:
+        assert not got[np.triu_indices(n, 1)].any()
+
+
+def test_softmax_minus_infinities():
+    s = synth.normal((1, 5, 701), 6, dtype="f32")
+    s[0, 1, :], s[0, 2, :700], s[0, 3, 5] = -np.inf, -np.inf, np.finfo(np.float32).min
+    p = [[0, 1], [0, 5], [0, 300, 701]]
+    S, P = upload(s, "f32", p), empty((1, 5, 701), "f32", p)
+    ea.joinagg("hqk->hqk", ea.OP_SOFTMAX, ea.AGG_LSE, [S], P)
+    got = values(P)[0]
+    assert not got[1].any()  # a row of -inf: zeros
+    assert got[2, 700] == 1.0 and not got[2, :700].any()
+    x = synth.to_f64(s, "f32")[0, [0, 3, 4]]
+    e = np.exp(x - x.max(1, keepdims=True))
+    assert_close(got[[0, 3, 4]], e / e.sum(1, keepdims=True), rel_fro=1e-5, what="finite rows")
