@@ -1649,14 +1649,21 @@ int get_joinagg_plan(const char* spec_str, const Spec& sp, int32_t join_op, int3
       int64_t slot_bytes = kGemmTM * kGemmTN * (int64_t)sizeof(float);
       // 128-row tiles where they are estimated cheaper: small and middle sizes,
       // which 256-row tiles either leave with few workgroups or split into
-      // many partial sums of 256 KiB.  (The 256-row model above leaves out
-      // launch, first loads and store, 5 us on every shape measured.)  The
-      // overrides of the 256-row plans, and EA_GEMM_TILE_M=256, keep those.
+      // many partial sums of 256 KiB.  The 256-row model above leaves out
+      // launch, first loads and store, 5 us on every shape measured, and that
+      // the last arriver of three or more parts reads them one after the other,
+      // 2.8 us each (SwiGLU 486 x 6016 x 400 in twelve parts: 50 us, modelled
+      // 16; 128-row tiles: 23).  The overrides of the 256-row plans, and
+      // EA_GEMM_TILE_M=256, keep those.
       const char* tile_m = getenv("EA_GEMM_TILE_M");
       if (p->gemm_direct && !getenv("EA_GEMM_SCHEDULE") && !getenv("EA_GEMM_TILE_N") && !(tile_m && atoi(tile_m) == 256)) {
         const int mtn = swiglu ? kGemmMidTN / 2 : kGemmMidTN;
         const GemmDlPlan dm = gemm_units_mid(ops[0], ops[sp.n_in], mtn);
-        if (dm.cost < dl.cost + 5.0 || (tile_m && atoi(tile_m) == 128)) {
+        int parts = 1;
+        for (const GemmUnit& u : dl.units)
+          for (int k = 0; k < u.n_seg; ++k) parts = std::max(parts, u.seg[k].n_parts);
+        const double left_out = 5.0 + (parts > 2 ? 2.8 * parts : 0.0);
+        if (dm.cost < dl.cost + left_out || (tile_m && atoi(tile_m) == 128)) {
           p->gemm_tm = kGemmMidTM;
           tn = mtn;
           dl = dm;
