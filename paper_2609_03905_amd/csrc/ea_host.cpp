@@ -373,22 +373,25 @@ void key_rel(std::ostringstream& k, const ea_relation* r) {
   }
 }
 
-// Layout ids: one per distinct (dtype, partition) a relation was created with.
-// The table grows with the distinct layouts of the process (a key of a few
-// numbers per split point), like the plan cache.
+// Layout ids: equal for relations of equal dtype and partition, never reused.
+// The table of known layouts is dropped when it is full; equal layouts on
+// either side of that have different ids, which costs the calls that use both
+// a full validation, no more.
+constexpr size_t kMaxLayouts = 65536;
 uint64_t layout_id(const ea_relation* r) {
   static std::mutex mu;
   static auto* ids = new std::unordered_map<std::string, uint64_t>();  // intentionally leaked at exit
+  static uint64_t last = 0;
   std::string k;
-  auto put = [&](const void* p, size_t n) { k.append(static_cast<const char*>(p), n); };
-  put(&r->dtype, sizeof(r->dtype));
-  for (int d = 0; d < r->rank; ++d) {  // every list starts at 0 and increases: the concatenation is unambiguous
-    put(r->splits[d].data(), r->splits[d].size() * sizeof(int64_t));
-  }
+  k.append(reinterpret_cast<const char*>(&r->dtype), sizeof(r->dtype));
+  for (int d = 0; d < r->rank; ++d)  // every list starts at 0 and increases: the concatenation is unambiguous
+    k.append(reinterpret_cast<const char*>(r->splits[d].data()), r->splits[d].size() * sizeof(int64_t));
   std::lock_guard<std::mutex> lk(mu);
   auto it = ids->find(k);
-  if (it == ids->end()) it = ids->emplace(std::move(k), ids->size() + 1).first;
-  return it->second;
+  if (it != ids->end()) return it->second;
+  if (ids->size() >= kMaxLayouts) ids->clear();
+  ids->emplace(std::move(k), ++last);
+  return last;
 }
 
 // Allocate a device buffer for a plan image and upload the image into it.
@@ -1844,18 +1847,31 @@ int prepare(const char* spec, int32_t join_op, int32_t agg_op, int32_t n_in, con
 }
 
 // Calls seen before: everything validation and planning look at (spec, ops,
-// operand layouts, parameters, device) maps to the resulting operation and
-// plan, so that a repeated call does neither again.  Only valid, planned calls
-// enter; data pointers are no part of it and are checked on every call.
+// operand layouts, parameters, device) maps to the plan and what else a run
+// needs, so that a repeated call does neither again.  Only valid, planned
+// calls enter; data pointers are no part of it and are checked on every call.
 struct Call {
-  OpInfo oi;
   Plan* plan = nullptr;
+  int32_t causal = 0, q_dim = 0, k_dim = 0;
 };
 std::unordered_map<std::string, Call>& calls() {  // guarded by g_cache_mu
   static auto* m = new std::unordered_map<std::string, Call>();  // intentionally leaked at exit
   return *m;
 }
-constexpr size_t kMaxCalls = 65536;  // beyond it (ever-changing parameters) calls are validated in full
+constexpr size_t kMaxCalls = 65536;  // dropped when full
+
+void remember_call(std::string key, const Call& c) {
+  std::lock_guard<std::mutex> lk(g_cache_mu);
+  if (calls().size() >= kMaxCalls) calls().clear();
+  calls().emplace(std::move(key), c);
+}
+bool known_call(const std::string& key, Call* c) {
+  std::lock_guard<std::mutex> lk(g_cache_mu);
+  auto it = calls().find(key);
+  if (it == calls().end()) return false;
+  *c = it->second;
+  return true;
+}
 
 template <class T>
 void put_raw(std::string* k, const T& v) {
@@ -1897,30 +1913,18 @@ std::string call_key(const char* spec, int32_t join_op, int32_t agg_op, int32_t 
 // Validate a join-agg call and find its plan; a missing plan is built when
 // `build` is set, else EA_ERR_NOPLAN.
 int find_call(const char* spec, int32_t join_op, int32_t agg_op, int32_t n_in, const ea_relation* const* in,
-              const ea_relation* out, const ea_params* params, bool need_data, bool build, hipStream_t s,
-              const Call** call) {
+              const ea_relation* out, const ea_params* params, bool need_data, bool build, hipStream_t s, Call* call) {
   int dev = 0;
   const bool have_dev = hipGetDevice(&dev) == hipSuccess;
-  const std::string key =
-      have_dev ? call_key(spec, join_op, agg_op, n_in, in, out, params, need_data, dev) : std::string();
-  if (!key.empty()) {
-    std::lock_guard<std::mutex> lk(g_cache_mu);
-    auto it = calls().find(key);
-    if (it != calls().end()) {
-      *call = &it->second;
-      return EA_OK;
-    }
-  }
-  thread_local Call slow;
+  std::string key = have_dev ? call_key(spec, join_op, agg_op, n_in, in, out, params, need_data, dev) : std::string();
+  if (!key.empty() && known_call(key, call)) return EA_OK;
   Spec sp;
-  slow.plan = nullptr;
-  int e = prepare(spec, join_op, agg_op, n_in, in, out, params, need_data, build, s, &sp, &slow.oi, &slow.plan);
+  OpInfo oi;
+  Plan* plan = nullptr;
+  int e = prepare(spec, join_op, agg_op, n_in, in, out, params, need_data, build, s, &sp, &oi, &plan);
   if (e) return e;
-  *call = &slow;
-  if (!key.empty()) {
-    std::lock_guard<std::mutex> lk(g_cache_mu);
-    if (calls().size() < kMaxCalls) calls().emplace(key, slow);
-  }
+  *call = Call{plan, oi.causal, oi.q_dim, oi.k_dim};
+  if (!key.empty()) remember_call(std::move(key), *call);
   return EA_OK;
 }
 
@@ -2145,8 +2149,9 @@ namespace {
 // Enqueue the kernels of a planned join-agg on stream s.  ws: the split-key
 // workspace (counters at its start, partial results from kWsCounterBytes),
 // at least plan->ws_bytes() bytes, or null when the plan needs none.
-int run_planned(const Plan* plan, int32_t join_op, int32_t n_in, const ea_relation* const* in, ea_relation* out,
-                const ea_params* params, const OpInfo& oi, char* ws, hipStream_t s) {
+int run_planned(const Call& call, int32_t join_op, int32_t n_in, const ea_relation* const* in, ea_relation* out,
+                const ea_params* params, char* ws, hipStream_t s) {
+  const Plan* plan = call.plan;
   const ea_relation* res = params ? params->residual : nullptr;
   switch (plan->kind) {
     case K_GENERIC: {
@@ -2242,7 +2247,7 @@ int run_planned(const Plan* plan, int32_t join_op, int32_t n_in, const ea_relati
       a.n_rowtasks = (int32_t)plan->n_work;
       a.tuple_stride = n_in + 1;
       a.rank = out->rank;
-      a.causal = oi.causal;
+      a.causal = call.causal;
       a.row_len = plan->rows.row_len;
       a.vec = plan->rows.vec;
       a.seg_chunks = plan->rows.cps;
@@ -2276,9 +2281,9 @@ int run_planned(const Plan* plan, int32_t join_op, int32_t n_in, const ea_relati
       a.o = (char*)out->data;
       a.units = (const AttnUnit*)plan->d_work;
       a.n_units = (int32_t)plan->n_work;
-      a.causal = oi.causal;
-      a.q_dim = oi.q_dim;
-      a.k_dim = oi.k_dim;
+      a.causal = call.causal;
+      a.q_dim = call.q_dim;
+      a.k_dim = call.k_dim;
       a.scale = params->scale;
       a.part_o = (float*)(ws + kWsCounterBytes);
       a.part_ml = (float*)(ws + kWsCounterBytes + plan->ws_part_ml);
@@ -2304,20 +2309,20 @@ int ea_joinagg_workspace(const char* spec, int32_t join_op, int32_t agg_op, int3
                          int64_t* ws_bytes, void* stream) {
   if (!ws_bytes) return fail(EA_ERR_ARG, "NULL ws_bytes");
   *ws_bytes = 0;
-  const Call* call = nullptr;
+  Call call;
   int e = find_call(spec, join_op, agg_op, n_in, in, out, params, false, true, (hipStream_t)stream, &call);
   if (e) return e;
-  *ws_bytes = call->plan->ws_bytes();
+  *ws_bytes = call.plan->ws_bytes();
   return ok();
 }
 
 int ea_joinagg(const char* spec, int32_t join_op, int32_t agg_op, int32_t n_in, const ea_relation* const* in,
                ea_relation* out, const ea_params* params, void* workspace, int64_t ws_bytes, void* stream) {
   hipStream_t s = (hipStream_t)stream;
-  const Call* call = nullptr;
+  Call call;
   int e = find_call(spec, join_op, agg_op, n_in, in, out, params, true, false, s, &call);
   if (e) return e;
-  const Plan* plan = call->plan;
+  const Plan* plan = call.plan;
   const int64_t need = plan->ws_bytes();
   if (need) {
     if (!workspace) return fail(EA_ERR_ARG, "this join-agg needs a workspace of %lld bytes", (long long)need);
@@ -2326,7 +2331,7 @@ int ea_joinagg(const char* spec, int32_t join_op, int32_t agg_op, int32_t n_in, 
       return fail(EA_ERR_CAPACITY, "workspace of %lld bytes below the %lld this join-agg needs", (long long)ws_bytes,
                   (long long)need);
   }
-  e = run_planned(plan, join_op, n_in, in, out, params, call->oi, need ? (char*)workspace : nullptr, s);
+  e = run_planned(call, join_op, n_in, in, out, params, need ? (char*)workspace : nullptr, s);
   if (e) return e;
   return ok();
 }
@@ -2334,10 +2339,10 @@ int ea_joinagg(const char* spec, int32_t join_op, int32_t agg_op, int32_t n_in, 
 int ea_joinagg_noalloc(const char* spec, int32_t join_op, int32_t agg_op, int32_t n_in, const ea_relation* const* in,
                        ea_relation* out, const ea_params* params, void* stream) {
   hipStream_t s = (hipStream_t)stream;
-  const Call* call = nullptr;
+  Call call;
   int e = find_call(spec, join_op, agg_op, n_in, in, out, params, true, false, s, &call);
   if (e) return e;
-  const Plan* plan = call->plan;
+  const Plan* plan = call.plan;
   const int64_t need = plan->ws_bytes();
   char* ws = nullptr;
   if (need) {
@@ -2354,7 +2359,7 @@ int ea_joinagg_noalloc(const char* spec, int32_t join_op, int32_t agg_op, int32_
       EA_HIP_TRY(hipGetLastError());
     }
   }
-  e = run_planned(plan, join_op, n_in, in, out, params, call->oi, ws, s);
+  e = run_planned(call, join_op, n_in, in, out, params, ws, s);
   if (e) return e;
   return ok();
 }
@@ -2387,9 +2392,20 @@ int check_repartition(const ea_relation* src, const ea_relation* dst, bool need_
 int get_repartition_plan(const ea_relation* src, const ea_relation* dst, bool build, hipStream_t s, Plan** out) {
   int dev = 0;
   EA_HIP_TRY(hipGetDevice(&dev));
-  char kb[64];
-  snprintf(kb, sizeof(kb), "R|%d|%llu|%llu", dev, (unsigned long long)src->layout, (unsigned long long)dst->layout);
-  const std::string key = kb;
+  std::string short_key("R\0", 2);  // (no join-agg call's key holds a spec "R")
+  put_raw(&short_key, dev);
+  put_raw(&short_key, src->layout);
+  put_raw(&short_key, dst->layout);
+  Call call;
+  if (known_call(short_key, &call)) {
+    *out = call.plan;
+    return EA_OK;
+  }
+  std::ostringstream k;
+  k << "R|" << dev;
+  key_rel(k, src);
+  key_rel(k, dst);
+  const std::string key = k.str();
   Plan* plan = nullptr;
   {
     std::lock_guard<std::mutex> lk(g_cache_mu);
@@ -2513,6 +2529,8 @@ int get_repartition_plan(const ea_relation* src, const ea_relation* dst, bool bu
       cache()[key] = std::move(p);
     }
   }
+  call.plan = plan;
+  remember_call(std::move(short_key), call);
   *out = plan;
   return EA_OK;
 }
