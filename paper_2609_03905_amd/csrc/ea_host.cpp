@@ -15,6 +15,7 @@
 #include <map>
 #include <memory>
 #include <mutex>
+#include <numeric>
 #include <sstream>
 #include <string>
 #include <unordered_map>
@@ -1030,8 +1031,8 @@ GemmPlanInfo gemm_units(const ea_relation* a, const ea_relation* c, int tn, doub
 // cheaper one is kept:
 //   * even: the tiles of gemm_units (split or not, in XCD-aware order), one
 //     segment each;
-//   * balanced: the tiles' 32-deep K steps laid end to end (tiles in block
-//     order) and cut into 256 equal runs, one per CU; a run may end one tile
+//   * balanced: the tiles' 32-deep K steps laid end to end (in an order for
+//     the L2s, below) and cut into 256 equal runs, one per CU; a run may end one tile
 //     and start the next, and a tile cut into several runs is merged by its
 //     last arriver.  This fills every CU when there are fewer tiles than CUs.
 // Time model (us): 0.75 per K step of a tile, 1 per segment (pipeline fill and
@@ -1041,8 +1042,8 @@ GemmPlanInfo gemm_units(const ea_relation* a, const ea_relation* c, int tn, doub
 // each.  The rate is above HBM's because those exchanges partly overlap
 // other workgroups' K steps; it is fitted to the block share, where balanced
 // SwiGLU (176 tiles, 176 steps per run, almost every tile in two or three
-// runs) measured 188 us against 191-194 us even, and balanced QKV 125 us
-// against 109-112 us even.
+// runs) measured 188 us against 191-194 us even (184 us with the order for
+// the L2s), and balanced QKV 125 us against 109-112 us even.
 // The step time grows once more than about 190 CUs run matrix work at once:
 // the sustained clock is power-limited, so a schedule that keeps all 256 CUs
 // busy gains less than its CU count suggests.
@@ -1118,6 +1119,45 @@ GemmDlPlan gemm_units_dl(const ea_relation* a, const ea_relation* c, int tn, con
   if (T == 0 || S == 0 || T >= kCUs) return ev;  // a full wave of tiles: nothing to balance
   const int64_t q = (total + kCUs - 1) / kCUs;    // steps per unit (< S: at most two tiles per unit)
   if (q < 8) return ev;                           // too little work per unit to share
+  // Order of the tiles on the line.  Runs start q steps apart, so run u is at
+  // step (u * q) mod S of its tile at any time: runs whose numbers agree modulo
+  // S / g (g = gcd(q, S)) walk K together, and they hold the tiles q / g apart.
+  // Where S / g is a multiple of 8 they are also on one XCD (workgroup i runs
+  // on XCD i % 8), so the panels that they have in common are read into its L2
+  // once; runs at other steps share nothing, the L2 holds about four steps.
+  // Each such class is therefore made a rectangle of two tile rows (in one
+  // sweep heights of 2 to 4 were within 3% of each other, 1 and 8 up to 5%
+  // slower).  Tiles in block order against this one, bf16, us (medians of
+  // three, both in turn on one card; 0.5% apart on either side):
+  //   SwiGLU 2048 x 8192 x 2752   187.5 | 184.0    [n][k]   192.7 | 187.7
+  //          1536 x 8192 x 3072   169.7 | 157.3
+  //          2048 x 8192 x 2304   160.6 | 152.8
+  //          1024 x 8192 x 5504   199.0 | 191.4
+  //          1024 x 4096 x 5504   101.1 | 101.5
+  //   plain  2560 x 8192 x 3584   192.2 | 153.1
+  //          2560 x 4096 x 3584   112.3 |  88.5
+  //          3072 x 4096 x 3584    91.1 |  90.9
+  //          3072 x 6144 x 3584   137.9 | 139.8
+  const int64_t g = std::gcd(q, S), period = q / g;
+  if (S / g % 8 == 0 && T > period) {
+    constexpr int64_t kStripe = 2;
+    std::vector<int64_t> mrow(c->nb[0] + 1, 0), ncol(c->nb[1] + 1, 0);
+    for (int b = 0; b < c->nb[0]; ++b)
+      mrow[b + 1] = mrow[b] + (c->splits[0][b + 1] - c->splits[0][b] + kGemmTM - 1) / kGemmTM;
+    for (int b = 0; b < c->nb[1]; ++b) ncol[b + 1] = ncol[b] + (c->splits[1][b + 1] - c->splits[1][b] + tn - 1) / tn;
+    auto key = [&](const GemmTile& t) {  // stripes of tile rows, walked column by column
+      int32_t co[kMaxRank];
+      block_coords(c, t.block, co);
+      const int64_t mi = mrow[co[0]] + t.m0 / kGemmTM, ni = ncol[co[1]] + t.n0 / tn;
+      return ((mi / kStripe) * ncol.back() + ni) * kStripe + mi % kStripe;
+    };
+    std::sort(tiles.begin(), tiles.end(), [&](const GemmTile& x, const GemmTile& y) { return key(x) < key(y); });
+    std::vector<GemmTile> line((size_t)T);
+    size_t next = 0;
+    for (int64_t r = 0; r < period; ++r)
+      for (int64_t t = r; t < T; t += period) line[(size_t)t] = tiles[next++];
+    tiles.swap(line);
+  }
   GemmDlPlan bal;
   bal.balanced = true;
   std::vector<std::vector<std::pair<int, int>>> segs_of(T);  // (unit, seg) per tile, ascending s0

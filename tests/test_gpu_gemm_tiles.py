@@ -96,3 +96,24 @@ def test_more_tuples_than_the_direct_kernels_hold():
     # 130 contracted blocks per output block: the register-staged kernel
     got, ref = _product("tj,jk->tk", 70, 72, [0, 70], list(range(0, 1041, 8)), [0, 72])
     np.testing.assert_array_equal(got, ref)
+
+
+@pytest.mark.parametrize("spec,T,J,pk", [
+    ("tj,jk,jk->tk", 400, 2048, [0, 512, 1024, 1536, 2048, 2560, 2904]),  # 46 tiles in 3 classes: 16, 15, 15
+    ("tj,jk->tk", 400, 8192, [0, 520, 1024, 2792]),                       # an odd number of tile columns
+    ("tj,kj->tk", 700, 8192, [0, 1000, 2048]),                            # three tile rows: half a stripe
+    ("tj,kj->tk", 520, 2000, [0, 3000]),                                  # runs in no common step: block order
+], ids=str)
+def test_balanced_runs(monkeypatch, spec, T, J, pk):
+    # equal runs of K steps, the tiles ordered for the runs that walk K together
+    monkeypatch.setenv("EA_GEMM_TILE_M", "256")
+    monkeypatch.setenv("EA_GEMM_SCHEDULE", "balanced")
+    ea.plan_cache_clear()
+    try:
+        got, ref = _product(spec, T, pk[-1], [0, 256, T], synth.splits(J, 512), pk)
+    finally:
+        ea.plan_cache_clear()
+    if spec.count("j") == 3:
+        assert_close(got, ref, rel_fro=1e-5, what=spec)
+    else:
+        np.testing.assert_array_equal(got, ref)
