@@ -328,8 +328,9 @@ struct Plan {
   int gemm_tn = kGemmTN;     // output tile columns per right operand (256, 128 or 64)
   int gemm_tm = kGemmTM;     // output tile rows (256, or 128)
   bool gemm_tail = false;    // some contracted block extent is no multiple of 32
+  bool gemm_balanced = false, gemm_by_class = false;  // the schedule (see gemm_units_dl)
   GemmTupleMeta* d_gemm_meta = nullptr;  // direct-load plans: per-tuple operand blocks
-  // contraction: everything of its arguments but the data pointers
+  // reduction and contraction: everything of their arguments but the data pointers
   ReduceArgs red;
   ContractArgs con;
   int con_a = 0;  // input that is the kernel's A
@@ -1051,7 +1052,8 @@ struct GemmDlPlan {
   std::vector<GemmUnit> units;
   int32_t slots = 0, counters = 0;
   bool balanced = false;
-  double cost = 0.0;  // the model's time of the kept schedule (us)
+  bool by_class = false;  // balanced: tiles ordered by runs in step, not by block
+  double cost = 0.0;      // the model's time of the kept schedule (us)
 };
 
 GemmDlPlan gemm_units_dl(const ea_relation* a, const ea_relation* c, int tn, const GemmPlanInfo& even,
@@ -1138,6 +1140,8 @@ GemmDlPlan gemm_units_dl(const ea_relation* a, const ea_relation* c, int tn, con
   //          2560 x 4096 x 3584   112.3 |  88.5
   //          3072 x 4096 x 3584    91.1 |  90.9
   //          3072 x 6144 x 3584   137.9 | 139.8
+  GemmDlPlan bal;
+  bal.balanced = true;
   const int64_t g = std::gcd(q, S), period = q / g;
   if (S / g % 8 == 0 && T > period) {
     constexpr int64_t kStripe = 2;
@@ -1157,9 +1161,8 @@ GemmDlPlan gemm_units_dl(const ea_relation* a, const ea_relation* c, int tn, con
     for (int64_t r = 0; r < period; ++r)
       for (int64_t t = r; t < T; t += period) line[(size_t)t] = tiles[next++];
     tiles.swap(line);
+    bal.by_class = true;
   }
-  GemmDlPlan bal;
-  bal.balanced = true;
   std::vector<std::vector<std::pair<int, int>>> segs_of(T);  // (unit, seg) per tile, ascending s0
   for (int64_t u0 = 0; u0 < total; u0 += q) {
     GemmUnit u;
@@ -1620,48 +1623,20 @@ int attention_units(const ea_relation* Q, const std::vector<int32_t>& goff, Attn
   return EA_OK;
 }
 
-// Look up or create the plan of a join-agg call.
-// Look up the plan of a join-agg configuration.  With build set, a missing
-// plan is created: its tables are uploaded, the GPU join enumerator runs on
-// stream s and the host waits for it (and, for attention, sizes the work
-// units from the GPU's group offsets).  Without build, a missing plan is
-// EA_ERR_NOPLAN: the enqueue path never allocates or synchronizes.
-int get_joinagg_plan(const char* spec_str, const Spec& sp, int32_t join_op, int32_t agg_op,
-                     const ea_relation* const* ops, const ea_params* prm, const OpInfo& oi, bool build,
-                     hipStream_t s, Plan** out) {
-  int dev = 0;
-  EA_HIP_TRY(hipGetDevice(&dev));
-  std::ostringstream k;
-  k << "J|" << dev << "|" << spec_str << "|" << join_op << "|" << agg_op << "|" << oi.causal << oi.join_causal
-    << "|g" << oi.gqa << "|s";
-  for (int64_t e : oi.seq_ends) k << e << ",";
-  for (int o = 0; o <= sp.n_in; ++o) key_rel(k, ops[o]);
-  const ea_relation* res = prm ? prm->residual : nullptr;
-  if (res && (oi.kind == K_GEMM || oi.kind == K_GENERIC || oi.kind == K_CONTRACT || oi.kind == K_REDUCE)) k << "|res" << res->dtype;
-  const std::string key = k.str();
-  std::lock_guard<std::mutex> lk(g_cache_mu);
-  auto it = cache().find(key);
-  if (it != cache().end()) {
-    *out = it->second.get();
-    return EA_OK;
-  }
-  if (!build)
-    return fail(EA_ERR_NOPLAN, "join-agg '%s' is not planned on device %d: call ea_joinagg_workspace first", spec_str,
-                dev);
+// The host part of a plan: its work list and tables as an image to upload, and
+// what the launches need besides.  No HIP call.
+int plan_image(const Spec& sp, int32_t join_op, int32_t agg_op, const ea_relation* const* ops, const ea_relation* res,
+               const OpInfo& oi, Plan* p, Image* img, JoinSections* js, Extra* ex) {
   JoinInfo ji;
   int e = analyze_join(sp, ops, oi.group, &ji);
   if (e) return e;
-  Image img;
-  JoinSections js;
-  auto p = std::make_unique<Plan>();
   p->kind = oi.kind;
   p->n_in = sp.n_in;
   p->b_kmajor = oi.b_kmajor;
-  e = build_join(sp, ops, ji, oi, &img, &js, &p->n_groups, &p->tuple_cap);
+  e = build_join(sp, ops, ji, oi, img, js, &p->n_groups, &p->tuple_cap);
   if (e) return e;
-  Extra ex;
   switch (oi.kind) {
-    case K_GENERIC: e = build_generic(sp, join_op, agg_op, ops, ji, res, &img, &ex); break;
+    case K_GENERIC: e = build_generic(sp, join_op, agg_op, ops, ji, res, img, ex); break;
     case K_GEMM: {
       const bool swiglu = join_op == EA_OP_SWIGLU;
       int tn = swiglu ? kGemmTNSwiglu : kGemmTN;
@@ -1717,33 +1692,71 @@ int get_joinagg_plan(const char* spec_str, const Spec& sp, int32_t join_op, int3
       p->gemm_parts = gi.parts;
       int64_t slots = gi.slots;
       if (p->gemm_direct) {
-        ex.work = img.put_vec(dl.units);
-        ex.n_work = (int64_t)dl.units.size();
-        ex.meta = img.put_zero((size_t)p->tuple_cap * sizeof(GemmTupleMeta));
+        ex->work = img->put_vec(dl.units);
+        ex->n_work = (int64_t)dl.units.size();
+        ex->meta = img->put_zero((size_t)p->tuple_cap * sizeof(GemmTupleMeta));
         slots = dl.slots;
         p->ws_counters = dl.counters;
+        p->gemm_balanced = dl.balanced;
+        p->gemm_by_class = dl.by_class;
       } else {
-        ex.work = img.put_vec(gi.units);
-        ex.n_work = (int64_t)gi.units.size();
+        ex->work = img->put_vec(gi.units);
+        ex->n_work = (int64_t)gi.units.size();
         p->ws_counters = gi.counters;
       }
       // fp32 partial tiles of split keys in the workspace
       p->ws_partial_bytes = slots * slot_bytes;
       break;
     }
-    case K_REDUCE: e = build_reduce(ops, sp.n_in, join_op, agg_op, oi.red, p->tuple_cap, &img, &ex, &p->red); break;
-    case K_CONTRACT: e = build_contract(ops, oi.con, p->tuple_cap, &img, &ex, &p->con); break;
+    case K_REDUCE: e = build_reduce(ops, sp.n_in, join_op, agg_op, oi.red, p->tuple_cap, img, ex, &p->red); break;
+    case K_CONTRACT: e = build_contract(ops, oi.con, p->tuple_cap, img, ex, &p->con); break;
     case K_RMSNORM:
-    case K_SOFTMAX: e = build_rows(sp, ops, oi, &img, &ex, &p->rows); break;
-    case K_ATTENTION: break;  // work units follow the GPU join (below)
+    case K_SOFTMAX: e = build_rows(sp, ops, oi, img, ex, &p->rows); break;
+    case K_ATTENTION: break;  // work units follow the GPU join
     default: e = fail(EA_ERR_UNSUPPORTED, "internal: unknown plan kind");
   }
+  if (e) return e;
+  p->n_work = ex->n_work;
+  return EA_OK;
+}
+
+// Look up the plan of a join-agg configuration.  With build set, a missing
+// plan is created: its tables are uploaded, the GPU join enumerator runs on
+// stream s and the host waits for it (and, for attention, sizes the work
+// units from the GPU's group offsets).  Without build, a missing plan is
+// EA_ERR_NOPLAN: the enqueue path never allocates or synchronizes.
+int get_joinagg_plan(const char* spec_str, const Spec& sp, int32_t join_op, int32_t agg_op,
+                     const ea_relation* const* ops, const ea_params* prm, const OpInfo& oi, bool build,
+                     hipStream_t s, Plan** out) {
+  int dev = 0;
+  EA_HIP_TRY(hipGetDevice(&dev));
+  std::ostringstream k;
+  k << "J|" << dev << "|" << spec_str << "|" << join_op << "|" << agg_op << "|" << oi.causal << oi.join_causal
+    << "|g" << oi.gqa << "|s";
+  for (int64_t e : oi.seq_ends) k << e << ",";
+  for (int o = 0; o <= sp.n_in; ++o) key_rel(k, ops[o]);
+  const ea_relation* res = prm ? prm->residual : nullptr;
+  if (res && (oi.kind == K_GEMM || oi.kind == K_GENERIC || oi.kind == K_CONTRACT || oi.kind == K_REDUCE)) k << "|res" << res->dtype;
+  const std::string key = k.str();
+  std::lock_guard<std::mutex> lk(g_cache_mu);
+  auto it = cache().find(key);
+  if (it != cache().end()) {
+    *out = it->second.get();
+    return EA_OK;
+  }
+  if (!build)
+    return fail(EA_ERR_NOPLAN, "join-agg '%s' is not planned on device %d: call ea_joinagg_workspace first", spec_str,
+                dev);
+  Image img;
+  JoinSections js;
+  Extra ex;
+  auto p = std::make_unique<Plan>();
+  int e = plan_image(sp, join_op, agg_op, ops, res, oi, p.get(), &img, &js, &ex);
   if (e) return e;
   e = plan_upload(p.get(), img, s);
   if (e) return e;
   p->d_desc = ex.desc ? p->dmem + ex.desc : nullptr;
   p->d_work = p->dmem + ex.work;
-  p->n_work = ex.n_work;
   e = finish_join(p.get(), js, sp.n_in + 1, s);
   if (e) return e;
   if (oi.kind == K_GEMM && p->gemm_direct) {
@@ -2598,6 +2611,47 @@ int ea_repartition_ex(const ea_relation* src, ea_relation* dst, int32_t store, v
   if (e) return e;
   EA_HIP_TRY(launch_repartition((const RepTask*)plan->d_work, plan->n_work, (const char*)src->data,
                                 (char*)dst->data, store == EA_STORE_STREAM, plan->rep_small, s));
+  return ok();
+}
+
+// The plan a call would get, as text (declared in ea_internal.h).
+int ea_internal_describe(const char* spec, int32_t join_op, int32_t agg_op, int32_t n_in, const ea_relation* const* in,
+                         const ea_relation* out, const ea_params* params, char* text, int64_t cap) {
+  Spec sp;
+  OpInfo oi;
+  int e = prepare(spec, join_op, agg_op, n_in, in, out, params, false, false, nullptr, &sp, &oi, nullptr);
+  if (e) return e;
+  const ea_relation* ops[kMaxOps];
+  for (int i = 0; i < n_in; ++i) ops[i] = in[i];
+  ops[n_in] = out;
+  Plan p;
+  Image img;
+  JoinSections js;
+  Extra ex;
+  e = plan_image(sp, join_op, agg_op, ops, params ? params->residual : nullptr, oi, &p, &img, &js, &ex);
+  if (e) return e;
+  std::ostringstream t;
+  int64_t threads = 256;
+  switch (p.kind) {
+    case K_GENERIC: t << "kind=generic"; break;
+    case K_GEMM:
+      threads = p.gemm_direct && p.gemm_tm == kGemmMidTM ? 256 : 512;
+      t << "kind=gemm direct=" << p.gemm_direct << " tile_m=" << p.gemm_tm << " tile_n=" << p.gemm_tn
+        << " tail=" << p.gemm_tail << " balanced=" << p.gemm_balanced << " by_class=" << p.gemm_by_class;
+      break;
+    case K_CONTRACT: t << "kind=contract tile=" << p.con.tile; break;
+    case K_REDUCE:
+      threads = p.red.threads;
+      t << "kind=reduce rows=" << p.red.rows << " share=" << p.red.R << " rounds=" << p.red.rounds;
+      break;
+    case K_RMSNORM: t << "kind=rmsnorm"; break;
+    case K_SOFTMAX: t << "kind=softmax"; break;
+    case K_ATTENTION: t << "kind=attention"; break;
+    default: t << "kind=other";
+  }
+  t << " work=" << p.n_work << " threads=" << threads << " table_bytes=" << img.bytes.size() << " ws=" << p.ws_bytes();
+  if (!text || cap < (int64_t)t.str().size() + 1) return fail(EA_ERR_CAPACITY, "describe: text buffer too small");
+  memcpy(text, t.str().c_str(), t.str().size() + 1);
   return ok();
 }
 

@@ -464,3 +464,10 @@ hipError_t launch_attention(const AttnArgs& a, hipStream_t s);
 hipError_t launch_attention_prep(const AttnArgs& a, hipStream_t s);
 
 }  // namespace ea
+
+// The plan a join-agg call would get, as "key=value ..." text: kernel, tile or
+// share, workgroups (work), threads of one, bytes of the plan's tables and of
+// the workspace.  Host only, no HIP call: for the tests of the dispatch rules.
+extern "C" int ea_internal_describe(const char* spec, int32_t join_op, int32_t agg_op, int32_t n_in,
+                                    const ea_relation* const* in, const ea_relation* out, const ea_params* params,
+                                    char* text, int64_t cap);

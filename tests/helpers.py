@@ -6,6 +6,8 @@ oracle again, so the product's layout is checked independently on every test.
 """
 from __future__ import annotations
 
+import ctypes
+
 import numpy as np
 import torch
 
@@ -85,3 +87,19 @@ def assert_close(got: np.ndarray, ref: np.ndarray, rel_fro: float = REL_FRO, max
     assert fro <= rel_fro, f"{what}: relative Frobenius error {fro:.3e} > {rel_fro:.1e}"
     assert mx <= max_abs_rel * scale + 1e-30, f"{what}: max |diff| {mx:.3e} > {max_abs_rel} * {scale:.3e}"
     return fro, mx
+
+
+def describe(spec, join_op, agg_op, operands, **params) -> dict:
+    """The plan a call would get, without a GPU: the library's dispatch
+    (ea_internal_describe) for operands given as (shape, dtype, partition),
+    the output last."""
+    rels = [ea.Relation(s, d, p, allocate=False) for s, d, p in operands]
+    n = len(rels) - 1
+    prm, _ends = ea._params(**params)
+    text = ctypes.create_string_buffer(512)
+    rc = ea.lib().ea_internal_describe(spec.encode(), join_op, agg_op, n,
+                                       (ctypes.c_void_p * n)(*[r.handle.value for r in rels[:n]]), rels[n].handle,
+                                       ctypes.byref(prm), text, ctypes.c_int64(len(text)))
+    assert rc == 0, ea.lib().ea_last_error()
+    out = dict(kv.split("=") for kv in text.value.decode().split())
+    return {k: v if k in ("kind", "path") else int(v) for k, v in out.items()}
