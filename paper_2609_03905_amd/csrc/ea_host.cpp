@@ -16,6 +16,7 @@
 #include <memory>
 #include <mutex>
 #include <numeric>
+#include <set>
 #include <sstream>
 #include <string>
 #include <unordered_map>
@@ -1043,8 +1044,8 @@ GemmPlanInfo gemm_units(const ea_relation* a, const ea_relation* c, int tn, doub
 // each.  The rate is above HBM's because those exchanges partly overlap
 // other workgroups' K steps; it is fitted to the block share, where balanced
 // SwiGLU (176 tiles, 176 steps per run, almost every tile in two or three
-// runs) measured 188 us against 191-194 us even (184 us with the order for
-// the L2s), and balanced QKV 125 us against 109-112 us even.
+// runs) measured 188 us against 191-194 us even, and balanced QKV 125 us
+// against 109-112 us even.
 // The step time grows once more than about 190 CUs run matrix work at once:
 // the sustained clock is power-limited, so a schedule that keeps all 256 CUs
 // busy gains less than its CU count suggests.
@@ -1056,7 +1057,8 @@ struct GemmDlPlan {
   double cost = 0.0;      // the model's time of the kept schedule (us)
 };
 
-GemmDlPlan gemm_units_dl(const ea_relation* a, const ea_relation* c, int tn, const GemmPlanInfo& even,
+// n_right: right operands (2 for SwiGLU), tn columns of each in a tile.
+GemmDlPlan gemm_units_dl(const ea_relation* a, const ea_relation* c, int tn, int n_right, const GemmPlanInfo& even,
                          double step_scale = 1.0) {
   const int kCUs = 256;
   const double t_step = 0.75 * step_scale, t_seg = 1.0, bw = 8.0e6, tile_bytes = (double)kGemmTM * tn * 4,
@@ -1129,17 +1131,18 @@ GemmDlPlan gemm_units_dl(const ea_relation* a, const ea_relation* c, int tn, con
   // once; runs at other steps share nothing, the L2 holds about four steps.
   // Each such class is therefore made a rectangle of two tile rows (in one
   // sweep heights of 2 to 4 were within 3% of each other, 1 and 8 up to 5%
-  // slower).  Tiles in block order against this one, bf16, us (medians of
-  // three, both in turn on one card; 0.5% apart on either side):
-  //   SwiGLU 2048 x 8192 x 2752   187.5 | 184.0    [n][k]   192.7 | 187.7
-  //          1536 x 8192 x 3072   169.7 | 157.3
-  //          2048 x 8192 x 2304   160.6 | 152.8
-  //          1024 x 8192 x 5504   199.0 | 191.4
-  //          1024 x 4096 x 5504   101.1 | 101.5
-  //   plain  2560 x 8192 x 3584   192.2 | 153.1
-  //          2560 x 4096 x 3584   112.3 |  88.5
-  //          3072 x 4096 x 3584    91.1 |  90.9
-  //          3072 x 6144 x 3584   137.9 | 139.8
+  // slower), where that cuts the panels that the classes fetch by a fifth or
+  // more; else the tiles stay in block order, whose classes are rectangles
+  // enough.  Panels fetched (of all tiles' panels) and time, bf16, block order
+  // | by class (medians of four, both in turn on one card, 0.5% apart):
+  //   SwiGLU 1792 x 8192 x 2752   1.00 | 0.75   211.5 | 158.9 us
+  //          1536 x 8192 x 3072   0.69 | 0.31   154.9 | 147.5
+  //          1024 x 8192 x 5504   0.69 | 0.51   181.8 | 174.2
+  //          2048 x 8192 x 2752   0.38 | 0.33   168.9 | 168.6 (kept in block order)
+  //          2048 x 8192 x 2304   0.35 | 0.33   150.0 | 148.9 (kept in block order)
+  //   plain  2560 x 8192 x 3584   1.00 | 0.50   193.0 | 147.1
+  //          2560 x 4096 x 3584   1.00 | 0.50   112.9 |  86.8
+  //          2304 x 6144 x 4096   0.73 | 0.34   131.5 | 118.4
   GemmDlPlan bal;
   bal.balanced = true;
   const int64_t g = std::gcd(q, S), period = q / g;
@@ -1149,19 +1152,36 @@ GemmDlPlan gemm_units_dl(const ea_relation* a, const ea_relation* c, int tn, con
     for (int b = 0; b < c->nb[0]; ++b)
       mrow[b + 1] = mrow[b] + (c->splits[0][b + 1] - c->splits[0][b] + kGemmTM - 1) / kGemmTM;
     for (int b = 0; b < c->nb[1]; ++b) ncol[b + 1] = ncol[b] + (c->splits[1][b + 1] - c->splits[1][b] + tn - 1) / tn;
-    auto key = [&](const GemmTile& t) {  // stripes of tile rows, walked column by column
+    auto place = [&](const GemmTile& t) {  // (tile row, tile column) in the whole grid
       int32_t co[kMaxRank];
       block_coords(c, t.block, co);
-      const int64_t mi = mrow[co[0]] + t.m0 / kGemmTM, ni = ncol[co[1]] + t.n0 / tn;
+      return std::pair<int64_t, int64_t>(mrow[co[0]] + t.m0 / kGemmTM, ncol[co[1]] + t.n0 / tn);
+    };
+    auto key = [&](const GemmTile& t) {  // stripes of tile rows, walked column by column
+      const auto [mi, ni] = place(t);
       return ((mi / kStripe) * ncol.back() + ni) * kStripe + mi % kStripe;
     };
-    std::sort(tiles.begin(), tiles.end(), [&](const GemmTile& x, const GemmTile& y) { return key(x) < key(y); });
-    std::vector<GemmTile> line((size_t)T);
+    std::vector<GemmTile> sorted = tiles, line((size_t)T);
+    std::sort(sorted.begin(), sorted.end(), [&](const GemmTile& x, const GemmTile& y) { return key(x) < key(y); });
     size_t next = 0;
     for (int64_t r = 0; r < period; ++r)
-      for (int64_t t = r; t < T; t += period) line[(size_t)t] = tiles[next++];
-    tiles.swap(line);
-    bal.by_class = true;
+      for (int64_t t = r; t < T; t += period) line[(size_t)t] = sorted[next++];
+    // rows of A and columns of B of the distinct panels of every class
+    auto fetched = [&](const std::vector<GemmTile>& l) {
+      int64_t n = 0;
+      for (int64_t r = 0; r < period; ++r) {
+        std::set<int64_t> rows, cols;
+        for (int64_t t = r; t < T; t += period) {
+          const auto [mi, ni] = place(l[(size_t)t]);
+          rows.insert(mi);
+          cols.insert(ni);
+        }
+        n += (int64_t)rows.size() * kGemmTM + (int64_t)cols.size() * tn * n_right;
+      }
+      return n;
+    };
+    bal.by_class = 5 * fetched(line) <= 4 * fetched(tiles);
+    if (bal.by_class) tiles.swap(line);
   }
   std::vector<std::vector<std::pair<int, int>>> segs_of(T);  // (unit, seg) per tile, ascending s0
   for (int64_t u0 = 0; u0 < total; u0 += q) {
@@ -1648,14 +1668,14 @@ int plan_image(const Spec& sp, int32_t join_op, int32_t agg_op, const ea_relatio
       p->gemm_direct = ops[0]->nb[1] <= kGemmMaxTuples && small;
       GemmPlanInfo gi = gemm_units(ops[0], ops[sp.n_in], tn);
       GemmDlPlan dl;
-      if (p->gemm_direct) dl = gemm_units_dl(ops[0], ops[sp.n_in], tn, gi);
+      if (p->gemm_direct) dl = gemm_units_dl(ops[0], ops[sp.n_in], tn, swiglu ? 2 : 1, gi);
       if (p->gemm_direct && !swiglu) {
         // 256 x 128 tiles: twice the workgroups for the same work, so fewer
         // split sums (or none) where 256-wide tiles leave CUs idle; a K step
         // of one costs kNarrowStep of a 256-wide one (the operand bytes per
         // MFMA rise by half)
         const GemmPlanInfo gn = gemm_units(ops[0], ops[sp.n_in], kGemmTNSwiglu, kNarrowStep);
-        const GemmDlPlan dn = gemm_units_dl(ops[0], ops[sp.n_in], kGemmTNSwiglu, gn, kNarrowStep);
+        const GemmDlPlan dn = gemm_units_dl(ops[0], ops[sp.n_in], kGemmTNSwiglu, 1, gn, kNarrowStep);
         const char* force = getenv("EA_GEMM_TILE_N");  // 128 or 256 overrides the model when a plan is built
         const bool narrow = force ? atoi(force) == 128 : dn.cost < dl.cost;
         if (narrow) {

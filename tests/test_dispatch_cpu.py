@@ -1,0 +1,26 @@
+"""Which plan a call gets: the dispatch rules of the host code, without a GPU."""
+import pytest
+
+import synth
+from helpers import describe
+from paper_2609_03905_amd import ea
+
+
+def _product(spec, ext, block=512, dtype="bf16", out=None, join=ea.JOIN_MUL, agg=ea.AGG_SUM, **kw):
+    """The plan of an einsum over letters of the given extents in blocks of
+    ``block`` (a number, or one per letter)."""
+    part = {x: synth.splits(n, min(n, block.get(x, n) if isinstance(block, dict) else block)) for x, n in ext.items()}
+    lhs, rhs = spec.split("->")
+    ops = [(tuple(ext[x] for x in s), dtype, [part[x] for x in s]) for s in lhs.split(",")]
+    ops.append((tuple(ext[x] for x in rhs), out or dtype, [part[x] for x in rhs]))
+    return describe(spec, join, agg, ops, **kw)
+
+
+@pytest.mark.parametrize("spec,t,j,k,by_class", [
+    ("tj,jk,jk->tk", 1792, 8192, 2752, 1), ("tj,jk,jk->tk", 1536, 8192, 3072, 1), ("tj,jk,jk->tk", 1024, 8192, 5504, 1),
+    ("tj,jk,jk->tk", 2048, 8192, 2752, 0), ("tj,kj,kj->tk", 2048, 8192, 2752, 0), ("tj,jk,jk->tk", 2048, 8192, 2304, 0),
+    ("tj,jk->tk", 2560, 8192, 3584, 1), ("tj,kj->tk", 2304, 6144, 4096, 1),
+])
+def test_balanced_tiles_are_reordered_only_where_panels_are_saved(spec, t, j, k, by_class):
+    d = _product(spec, dict(t=t, j=j, k=k), join=ea.OP_SWIGLU if spec.count("j") == 3 else ea.JOIN_MUL)
+    assert (d["kind"], d["balanced"], d["by_class"]) == ("gemm", 1, by_class)

@@ -100,12 +100,14 @@ def test_more_tuples_than_the_direct_kernels_hold():
 
 @pytest.mark.parametrize("spec,T,J,pk", [
     ("tj,jk,jk->tk", 400, 2048, [0, 512, 1024, 1536, 2048, 2560, 2904]),  # 46 tiles in 3 classes: 16, 15, 15
-    ("tj,jk->tk", 400, 8192, [0, 520, 1024, 2792]),                       # an odd number of tile columns
-    ("tj,kj->tk", 700, 8192, [0, 1000, 2048]),                            # three tile rows: half a stripe
+    ("tj,jk->tk", 400, 8192, [0, 520, 1024, 2792]),                       # panels shared in block order: kept
+    ("tj,kj->tk", 700, 8192, [0, 1000, 2048]),                            # the same
+    ("tj,kj->tk", 700, 8192, [0, 1000, 1408]),                            # three tile rows: half a stripe
+    ("tj,jk->tk", 700, 4096, [0, 512, 1024, 1152]),                       # 256 x 128 tiles, an odd number of columns
     ("tj,kj->tk", 520, 2000, [0, 3000]),                                  # runs in no common step: block order
 ], ids=str)
 def test_balanced_runs(monkeypatch, spec, T, J, pk):
-    # equal runs of K steps, the tiles ordered for the runs that walk K together
+    # equal runs of K steps, the tiles in block order or ordered for the runs that walk K together
     monkeypatch.setenv("EA_GEMM_TILE_M", "256")
     monkeypatch.setenv("EA_GEMM_SCHEDULE", "balanced")
     ea.plan_cache_clear()
