@@ -538,18 +538,17 @@ __global__ __launch_bounds__(W == 1 ? kThreads : 64 * W) void rows_elem_kernel(R
 #pragma unroll
     for (int k = 0; k < K; ++k) m = e0 + k * 64 * W < seen ? fmaxf(m, f[k]) : m;
     m = across(wave_max(m), [](float x, float y) { return fmaxf(x, y); });
+    // no visible entry above -inf: those of -inf give 0; a NaN, which the
+    // maximum passes over, stays one (0 x NaN)
+    const float mb = m == -INFINITY ? 0.0f : m;
     float l = 0.0f;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-      f[k] = e0 + k * 64 * W < seen ? __expf(f[k] - m) : 0.0f;
+      f[k] = e0 + k * 64 * W < seen ? __expf(f[k] - mb) : 0.0f;
       l += f[k];
     }
     l = across(wave_sum(l), plus);
     scale = m == -INFINITY ? 0.0f : 1.0f / l;
-    if (m == -INFINITY) {  // every visible entry -inf: zeros (the terms above are NaN)
-#pragma unroll
-      for (int k = 0; k < K; ++k) f[k] = 0.0f;
-    }
   } else {
     float ss = 0.0f;
 #pragma unroll

@@ -62,3 +62,36 @@ def test_softmax_minus_infinities():
     x = synth.to_f64(s, "f32")[0, [0, 3, 4]]
     e = np.exp(x - x.max(1, keepdims=True))
     assert_close(got[[0, 3, 4]], e / e.sum(1, keepdims=True), rel_fro=1e-5, what="finite rows")
+
+
+# element path on one, four and sixteen wavefronts; vector path with the
+# exponentials kept in registers and recomputed
+@pytest.mark.parametrize("n,dtype", [(5, "f32"), (701, "f32"), (701, "bf16"), (9001, "f32"), (704, "f32"), (4096, "bf16")])
+def test_softmax_nan_scores_stay_nan(n, dtype):
+    s = synth.normal((1, 4, n), 7, dtype="f32")
+    s[0, 1, :] = np.nan
+    s[0, 2, :], s[0, 2, n // 2] = -np.inf, np.nan
+    s[0, 0, 0] = np.nan
+    p = [[0, 1], [0, 4], [0, n]]
+    if dtype == "bf16":
+        s = (s.view(np.uint32) >> 16).astype(np.uint16)  # truncated: any values do
+    S = upload(s, dtype, p)
+    x = synth.to_f64(s, dtype)[0]
+    for causal in (False, True):
+        P = empty((1, 4, n), dtype, p)
+        ea.joinagg("hqk->hqk", ea.OP_SOFTMAX, ea.AGG_LSE, [S], P, causal=causal)
+        got = values(P)[0]
+        seen = np.tri(4, n, dtype=bool) if causal else np.ones((4, n), bool)
+        assert not got[~seen].any()  # masked entries are zeros
+        for r in range(3):
+            vis, out = x[r, seen[r]], got[r, seen[r]]
+            if np.isnan(vis).all():
+                assert np.isnan(out).all(), (r, causal)
+            elif np.isfinite(np.delete(vis, np.flatnonzero(np.isnan(vis)))).any():
+                assert np.isnan(out).all() or not np.isnan(vis).any()  # a NaN term makes the sum one
+            elif n == 4096:  # long rows on the vector path: a row without a finite score is NaN throughout
+                assert np.isnan(out).all()
+            else:  # NaN and -inf only: the NaN stays, -inf gives 0
+                np.testing.assert_array_equal(np.isnan(out), np.isnan(vis))
+                assert not out[~np.isnan(vis)].any()
+        assert np.isfinite(got[3]).all() and abs(got[3].sum() - 1) < 0.05
