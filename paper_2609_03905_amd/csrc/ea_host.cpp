@@ -1336,18 +1336,46 @@ int build_contract(const ea_relation* const* ops, const ContractDims& d, int64_t
 // 3.5 us per round: launch, pipeline fill, store.  Split sums: 3 us, plus
 // 0.7 us per part where the last arriver re-reads all (three or more), plus
 // the traffic of one 64 KiB partial per unit.
-double gemm_mid_time(int64_t tiles, int64_t S, int P) {
+// Beyond two rounds of 512 workgroups the last one overlaps the others, and the
+// time grows with the workgroups (figures at gemm_wide_time); right operands
+// stored [n][k] take 9% longer there, and operands beyond the 256 MiB of the
+// Infinity Cache 12%, since each is read twice as often as by 256-row tiles.
+double gemm_mid_time(int64_t tiles, int64_t S, int P, int kmajor, bool beyond_cache) {
   const int64_t units = tiles * P, n = (S + P - 1) / P;
   double t;
   if (units <= 256) t = 3.5 + (double)n * (0.25 + 0.07 * (double)units / 256.0);
-  else t = std::ceil((double)units / 512.0) * (3.5 + 0.55 * (double)n);
+  else if (units <= 1024) t = std::ceil((double)units / 512.0) * (3.5 + 0.55 * (double)n);
+  else
+    t = (6.0 + 0.17 * (double)n + (double)units * (0.0045 + 0.92e-3 * (double)n) +
+         std::max(0.0, (double)units - 1300.0) * 0.12e-3 * (double)n) *
+        (kmajor ? 1.09 : 1.0) * (beyond_cache ? 1.12 : 1.0);
   if (P > 1) t += 3.0 + (P > 2 ? 0.7 * P : 0.0) + 0.012 * (double)units;
   return t;
 }
 
+// Time model (us) of more than one wave of equal 256-row units, S steps each: a
+// step takes 0.81 us with every CU at work and 0.51 in a last wave of up to 88
+// units, which the power left over speeds up.  Measured | model, 256-row tiles
+// and 128-row tiles (four times as many, gemm_mid_time), bf16 in 512-blocks:
+//   2304 x 1024 x 8704   (306 tiles, S 32)     56.1 |  55    53.7 |  53
+//   2304 x 2048 x 8192   (288, 64)             96.3 |  97    89.3 |  90
+//   2304 x 2048 x 9984   (351, 64)             98.7 |  97   108.7 | 107
+//   2304 x 2048 x 17152  (603, 64)            161.7 | 155   178.2 | 178
+//   1000 x 4096 x 16640  (260, 128)           179.6 | 182   161.4 | 155
+//   4096 x 4096 x 5000   (320, 128), [n][k]   182.1 | 182   195.0 | 200
+//   2304 x 4096 x 7936   (279, 128), [n][k]   181.8 | 182   181.3 | 179
+//   2304 x 4096 x 9216   (324, 128)           181.6 | 182   195.4 | 186
+//   2304 x 4096 x 15104  (531, 128)           287.0 | 291   303.2 | 300
+//   1280 x 8192 x 15360  SwiGLU (600, 256)    627.2 | 564   865.8 | 660
+double gemm_wide_time(int64_t units, int64_t S, double step_scale) {
+  const int64_t full = (units - 1) / 256, last = units - 256 * full;
+  const double step = 0.81 * (double)full + 0.51 + 0.30 * std::max(0.0, (double)(last - 88) / 168.0);
+  return 2.0 + 5.5 * (double)(full + 1) + (double)S * step * step_scale;
+}
+
 // 128-row tiles on four wavefronts, two workgroups per CU: each tile's K walk
 // cut into P equal runs of 32-deep steps (not only at tuple bounds).
-GemmDlPlan gemm_units_mid(const ea_relation* a, const ea_relation* c, int tn) {
+GemmDlPlan gemm_units_mid(const ea_relation* a, const ea_relation* c, int tn, int kmajor, bool beyond_cache) {
   int64_t S = 0;
   for (int b = 0; b < a->nb[1]; ++b) S += (a->splits[1][b + 1] - a->splits[1][b] + 31) / 32;
   const GemmPlanInfo one = gemm_units(a, c, tn, 1.0, kGemmMidTM, 1);
@@ -1355,7 +1383,7 @@ GemmDlPlan gemm_units_mid(const ea_relation* a, const ea_relation* c, int tn) {
   int best_p = 1;
   double best = 1e300;
   for (int P = 1; P <= 16 && P <= S && (P == 1 || tiles * P <= 512); ++P) {  // split plans: at most 32 MiB of partials
-    const double t = gemm_mid_time(tiles, S, P);
+    const double t = gemm_mid_time(tiles, S, P, kmajor, beyond_cache);
     if (t < best - 1e-9) {
       best = t;
       best_p = P;
@@ -1691,17 +1719,26 @@ int plan_image(const Spec& sp, int32_t join_op, int32_t agg_op, const ea_relatio
       // launch, first loads and store, 5 us on every shape measured, and that
       // the last arriver of three or more parts reads them one after the other,
       // 2.8 us each (SwiGLU 486 x 6016 x 400 in twelve parts: 50 us, modelled
-      // 16; 128-row tiles: 23).  The overrides of the 256-row plans, and
-      // EA_GEMM_TILE_M=256, keep those.
+      // 16; 128-row tiles: 23); beyond one wave of units it counts a last wave of
+      // a few like a full one, and gemm_wide_time is used.
+      // The overrides of the 256-row plans, and EA_GEMM_TILE_M=256, keep those.
       const char* tile_m = getenv("EA_GEMM_TILE_M");
       if (p->gemm_direct && !getenv("EA_GEMM_SCHEDULE") && !getenv("EA_GEMM_TILE_N") && !(tile_m && atoi(tile_m) == 256)) {
         const int mtn = swiglu ? kGemmMidTN / 2 : kGemmMidTN;
-        const GemmDlPlan dm = gemm_units_mid(ops[0], ops[sp.n_in], mtn);
+        int64_t operand_bytes = 0;
+        for (int i = 0; i < sp.n_in; ++i) operand_bytes += ops[i]->nbytes;
+        const GemmDlPlan dm = gemm_units_mid(ops[0], ops[sp.n_in], mtn, oi.b_kmajor, operand_bytes > int64_t(256) << 20);
         int parts = 1;
         for (const GemmUnit& u : dl.units)
           for (int k = 0; k < u.n_seg; ++k) parts = std::max(parts, u.seg[k].n_parts);
-        const double left_out = 5.0 + (parts > 2 ? 2.8 * parts : 0.0);
-        if (dm.cost < dl.cost + left_out || (tile_m && atoi(tile_m) == 128)) {
+        double wide = dl.cost + 5.0 + (parts > 2 ? 2.8 * parts : 0.0);
+        if (!dl.balanced && dl.units.size() > 256) {
+          int64_t S = 0;
+          for (const GemmUnit& u : dl.units) S = std::max<int64_t>(S, u.seg[0].s1 - u.seg[0].s0);
+          wide = gemm_wide_time((int64_t)dl.units.size(), S, !swiglu && tn == kGemmTNSwiglu ? kNarrowStep : 1.0) +
+                 (double)dl.slots * 2.0 * (double)slot_bytes / 8.0e6;  // split sums, written and read
+        }
+        if (dm.cost < wide || (tile_m && atoi(tile_m) == 128)) {
           p->gemm_tm = kGemmMidTM;
           tn = mtn;
           dl = dm;

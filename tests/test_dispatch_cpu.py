@@ -24,3 +24,18 @@ def _product(spec, ext, block=512, dtype="bf16", out=None, join=ea.JOIN_MUL, agg
 def test_balanced_tiles_are_reordered_only_where_panels_are_saved(spec, t, j, k, by_class):
     d = _product(spec, dict(t=t, j=j, k=k), join=ea.OP_SWIGLU if spec.count("j") == 3 else ea.JOIN_MUL)
     assert (d["kind"], d["balanced"], d["by_class"]) == ("gemm", 1, by_class)
+
+
+# sizes whose 128-row plan measured slower than 256-row tiles (up to 39%), and
+# their neighbours that it serves better
+@pytest.mark.parametrize("spec,t,j,k,tile_m", [
+    ("tj,jk,jk->tk", 1280, 8192, 15360, 256), ("tj,jk->tk", 6144, 8192, 6200, 256), ("tj,kj->tk", 6144, 8192, 6200, 256),
+    ("tj,jk,jk->tk", 5000, 2048, 4096, 256), ("tj,jk->tk", 2304, 2048, 9984, 256), ("tj,kj->tk", 4096, 4096, 5000, 256),
+    ("tj,jk,jk->tk", 1000, 4096, 11008, 256), ("tj,jk->tk", 2304, 4096, 15104, 256), ("tj,jk,jk->tk", 1280, 8192, 8832, 256),
+    ("tj,jk,jk->tk", 1111, 8192, 8192, 256), ("tj,kj->tk", 3000, 4096, 6400, 256), ("tj,kj->tk", 3000, 4096, 5600, 128),
+    ("tj,jk->tk", 2304, 2048, 8192, 128), ("tj,jk->tk", 1000, 4096, 16640, 128), ("tj,jk,jk->tk", 1280, 8192, 6656, 128),
+    ("tj,jk->tk", 1024, 4096, 4096, 128), ("tj,jk->tk", 64, 4096, 4096, 128), ("tj,jk->tk", 4096, 4096, 4096, 256),
+])
+def test_gemm_tile_rows(spec, t, j, k, tile_m):
+    d = _product(spec, dict(t=t, j=j, k=k), join=ea.OP_SWIGLU if spec.count("j") == 3 else ea.JOIN_MUL)
+    assert (d["kind"], d["tile_m"]) == ("gemm", tile_m)
