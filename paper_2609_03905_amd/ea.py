@@ -21,6 +21,7 @@ OK = 0
 ERR_NAMES = {-1: "EA_ERR_ARG", -2: "EA_ERR_DTYPE", -3: "EA_ERR_PARTITION", -4: "EA_ERR_CAPACITY",
              -5: "EA_ERR_SPEC", -6: "EA_ERR_JOIN", -7: "EA_ERR_UNSUPPORTED", -8: "EA_ERR_HIP",
              -9: "EA_ERR_NOPLAN"}
+ERR_ARG, ERR_CAPACITY, ERR_NOPLAN = -1, -4, -9
 WS_COUNTER_BYTES = 262144  # EA_WS_COUNTER_BYTES: the counter area at the start of a workspace
 F32, BF16, F16 = 0, 1, 2
 DTYPES = {"f32": F32, "bf16": BF16, "f16": F16}
@@ -275,9 +276,11 @@ def joinagg(spec: str, join_op: int, agg_op: int, inputs: Sequence[Relation], ou
     prm, _ends = _params(eps, scale, causal, store, residual, gqa_group, seq_ends)
     s = _stream(stream)
     spec_b, prm_p, n_in = spec.encode(), ctypes.byref(prm), len(inputs)
-    # A planned configuration whose workspace fits runs at once; otherwise it
-    # is planned first and the workspace grown.  Any other failure comes again
-    # from the planning call or the second run.
+    # A planned configuration whose workspace fits runs at once.  Where the
+    # plan is missing, or the workspace (EA_ERR_ARG without one) or its size,
+    # all of which are found before anything is enqueued, it is planned, the
+    # workspace grown, and the call made again; any other error is raised: after
+    # EA_ERR_HIP the kernels may be queued already.
     buf = workspace
     if buf is None and _WS:
         buf = _WS.get((torch.cuda.current_device(), s or 0))
@@ -285,8 +288,11 @@ def joinagg(spec: str, join_op: int, agg_op: int, inputs: Sequence[Relation], ou
         ws, nbytes = None, 0
     else:
         ws, nbytes = buf.data_ptr(), buf.numel() * buf.element_size()
-    if lib().ea_joinagg(spec_b, join_op, agg_op, n_in, handles, out._h, prm_p, ws, nbytes, s) == OK:
+    rc = lib().ea_joinagg(spec_b, join_op, agg_op, n_in, handles, out._h, prm_p, ws, nbytes, s)
+    if rc == OK:
         return
+    if rc not in (ERR_NOPLAN, ERR_CAPACITY) and not (rc == ERR_ARG and ws is None):
+        _check(rc)
     need = ctypes.c_int64()
     _check(lib().ea_joinagg_workspace(spec_b, join_op, agg_op, n_in, handles, out._h, prm_p, ctypes.byref(need), s))
     ws, nbytes = None, 0
@@ -318,8 +324,11 @@ def repartition(src: Relation, dst: Relation, stream=None, *, store: int = 0) ->
     """Write ``src``'s dense tensor into ``dst`` under ``dst``'s partition
     (``store`` as for joinagg); planned on first use."""
     s = _stream(stream)
-    if lib().ea_repartition_ex(src._h, dst._h, int(store), s) == OK:
+    rc = lib().ea_repartition_ex(src._h, dst._h, int(store), s)
+    if rc == OK:
         return
+    if rc != ERR_NOPLAN:
+        _check(rc)
     _check(lib().ea_repartition_plan(src._h, dst._h, s))
     _check(lib().ea_repartition_ex(src._h, dst._h, int(store), s))
 
