@@ -362,6 +362,7 @@ struct Plan {
 };
 
 std::mutex g_cache_mu;
+uint64_t g_generation = 0;  // of the plan cache, guarded by g_cache_mu: clearing it starts the next
 std::map<std::string, std::unique_ptr<Plan>>& cache() {
   static auto* m = new std::map<std::string, std::unique_ptr<Plan>>();  // intentionally leaked at exit
   return *m;
@@ -1784,7 +1785,7 @@ int plan_image(const Spec& sp, int32_t join_op, int32_t agg_op, const ea_relatio
 // EA_ERR_NOPLAN: the enqueue path never allocates or synchronizes.
 int get_joinagg_plan(const char* spec_str, const Spec& sp, int32_t join_op, int32_t agg_op,
                      const ea_relation* const* ops, const ea_params* prm, const OpInfo& oi, bool build,
-                     hipStream_t s, Plan** out) {
+                     hipStream_t s, Plan** out, uint64_t* generation) {
   int dev = 0;
   EA_HIP_TRY(hipGetDevice(&dev));
   std::ostringstream k;
@@ -1796,6 +1797,7 @@ int get_joinagg_plan(const char* spec_str, const Spec& sp, int32_t join_op, int3
   if (res && (oi.kind == K_GEMM || oi.kind == K_GENERIC || oi.kind == K_CONTRACT || oi.kind == K_REDUCE)) k << "|res" << res->dtype;
   const std::string key = k.str();
   std::lock_guard<std::mutex> lk(g_cache_mu);
+  *generation = g_generation;
   auto it = cache().find(key);
   if (it != cache().end()) {
     *out = it->second.get();
@@ -1922,7 +1924,7 @@ int check_rel(const ea_relation* r, const char* what, bool need_data) {
 // Common front half of ea_joinagg / ea_join_tuples: validation + plan.
 int prepare(const char* spec, int32_t join_op, int32_t agg_op, int32_t n_in, const ea_relation* const* in,
             const ea_relation* out, const ea_params* prm, bool need_data, bool build, hipStream_t s, Spec* sp,
-            OpInfo* oi, Plan** plan) {
+            OpInfo* oi, Plan** plan, uint64_t* generation) {
   if (!spec) return fail(EA_ERR_ARG, "NULL spec");
   if (n_in < 1 || n_in > kMaxIn || !in) return fail(EA_ERR_ARG, "n_in %d outside [1, %d] or NULL inputs", n_in, kMaxIn);
   for (int i = 0; i < n_in; ++i) {
@@ -1953,7 +1955,7 @@ int prepare(const char* spec, int32_t join_op, int32_t agg_op, int32_t n_in, con
   e = analyze_join(*sp, ops, oi->group, &ji);
   if (e) return e;
   if (!plan) return EA_OK;
-  return get_joinagg_plan(spec, *sp, join_op, agg_op, ops, prm, *oi, build, s, plan);
+  return get_joinagg_plan(spec, *sp, join_op, agg_op, ops, prm, *oi, build, s, plan, generation);
 }
 
 // Calls seen before: everything validation and planning look at (spec, ops,
@@ -1970,10 +1972,14 @@ std::unordered_map<std::string, Call>& calls() {  // guarded by g_cache_mu
 }
 constexpr size_t kMaxCalls = 65536;  // dropped when full
 
-void remember_call(std::string key, const Call& c) {
+// Enters a call whose plan was found in `generation`.  A cache cleared since then
+// has freed the plan: the call is not entered.
+bool remember_call(std::string key, const Call& c, uint64_t generation) {
   std::lock_guard<std::mutex> lk(g_cache_mu);
+  if (generation != g_generation) return false;
   if (calls().size() >= kMaxCalls) calls().clear();
   calls().emplace(std::move(key), c);
+  return true;
 }
 bool known_call(const std::string& key, Call* c) {
   std::lock_guard<std::mutex> lk(g_cache_mu);
@@ -2031,10 +2037,11 @@ int find_call(const char* spec, int32_t join_op, int32_t agg_op, int32_t n_in, c
   Spec sp;
   OpInfo oi;
   Plan* plan = nullptr;
-  int e = prepare(spec, join_op, agg_op, n_in, in, out, params, need_data, build, s, &sp, &oi, &plan);
+  uint64_t generation = 0;
+  int e = prepare(spec, join_op, agg_op, n_in, in, out, params, need_data, build, s, &sp, &oi, &plan, &generation);
   if (e) return e;
   *call = Call{plan, oi.causal, oi.q_dim, oi.k_dim};
-  if (!key.empty()) remember_call(std::move(key), *call);
+  if (!key.empty()) remember_call(std::move(key), *call, generation);
   return EA_OK;
 }
 
@@ -2229,7 +2236,8 @@ int ea_join_tuples(const char* spec, int32_t join_op, int32_t n_in, const ea_rel
   Spec sp;
   OpInfo oi;
   Plan* plan = nullptr;
-  int e = prepare(spec, join_op, agg, n_in, in, out, params, false, true, s, &sp, &oi, &plan);
+  uint64_t generation = 0;
+  int e = prepare(spec, join_op, agg, n_in, in, out, params, false, true, s, &sp, &oi, &plan, &generation);
   if (e) return e;
   int32_t count = 0;
   EA_HIP_TRY(hipMemcpyAsync(&count, plan->d_count, sizeof(int32_t), hipMemcpyDeviceToHost, s));
@@ -2517,8 +2525,10 @@ int get_repartition_plan(const ea_relation* src, const ea_relation* dst, bool bu
   key_rel(k, dst);
   const std::string key = k.str();
   Plan* plan = nullptr;
+  uint64_t generation = 0;
   {
     std::lock_guard<std::mutex> lk(g_cache_mu);
+    generation = g_generation;
     auto it = cache().find(key);
     if (it != cache().end()) plan = it->second.get();
     if (!plan && !build)
@@ -2640,7 +2650,7 @@ int get_repartition_plan(const ea_relation* src, const ea_relation* dst, bool bu
     }
   }
   call.plan = plan;
-  remember_call(std::move(short_key), call);
+  remember_call(std::move(short_key), call, generation);
   *out = plan;
   return EA_OK;
 }
@@ -2676,7 +2686,7 @@ int ea_internal_describe(const char* spec, int32_t join_op, int32_t agg_op, int3
                          const ea_relation* out, const ea_params* params, char* text, int64_t cap) {
   Spec sp;
   OpInfo oi;
-  int e = prepare(spec, join_op, agg_op, n_in, in, out, params, false, false, nullptr, &sp, &oi, nullptr);
+  int e = prepare(spec, join_op, agg_op, n_in, in, out, params, false, false, nullptr, &sp, &oi, nullptr, nullptr);
   if (e) return e;
   const ea_relation* ops[kMaxOps];
   for (int i = 0; i < n_in; ++i) ops[i] = in[i];
@@ -2712,6 +2722,13 @@ int ea_internal_describe(const char* spec, int32_t join_op, int32_t agg_op, int3
   return ok();
 }
 
+// The table of recognised calls, for tests (declared in ea_internal.h).
+uint64_t ea_internal_generation(void) {
+  std::lock_guard<std::mutex> lk(g_cache_mu);
+  return g_generation;
+}
+int ea_internal_remember(const char* key, uint64_t generation) { return remember_call(key, Call(), generation); }
+
 int64_t ea_plan_cache_size(void) {
   std::lock_guard<std::mutex> lk(g_cache_mu);
   return (int64_t)cache().size();
@@ -2719,6 +2736,7 @@ int64_t ea_plan_cache_size(void) {
 
 int ea_plan_cache_clear(void) {
   std::lock_guard<std::mutex> lk(g_cache_mu);
+  ++g_generation;
   calls().clear();  // they point into the plans
   cache().clear();
   return ok();

@@ -471,3 +471,9 @@ hipError_t launch_attention_prep(const AttnArgs& a, hipStream_t s);
 extern "C" int ea_internal_describe(const char* spec, int32_t join_op, int32_t agg_op, int32_t n_in,
                                     const ea_relation* const* in, const ea_relation* out, const ea_params* params,
                                     char* text, int64_t cap);
+
+// The plan cache's generation, and whether a call found in `generation` is
+// entered into the table of recognised calls (under a key of the test's own,
+// with no plan): for the tests of that table.
+extern "C" uint64_t ea_internal_generation(void);
+extern "C" int ea_internal_remember(const char* key, uint64_t generation);

@@ -1,4 +1,6 @@
 """Which plan a call gets: the dispatch rules of the host code, without a GPU."""
+import ctypes
+
 import pytest
 
 import synth
@@ -39,3 +41,16 @@ def test_balanced_tiles_are_reordered_only_where_panels_are_saved(spec, t, j, k,
 def test_gemm_tile_rows(spec, t, j, k, tile_m):
     d = _product(spec, dict(t=t, j=j, k=k), join=ea.OP_SWIGLU if spec.count("j") == 3 else ea.JOIN_MUL)
     assert (d["kind"], d["tile_m"]) == ("gemm", tile_m)
+
+
+def test_a_plan_cleared_meanwhile_is_not_recognised():
+    # a call finds its plan, the cache is cleared (another thread), then the
+    # call would be entered: its plan is gone
+    L = ea.lib()
+    L.ea_internal_generation.restype = ctypes.c_uint64
+    remember = lambda g: L.ea_internal_remember(b"a test's call", ctypes.c_uint64(g))
+    found_in = L.ea_internal_generation()
+    ea.plan_cache_clear()
+    assert remember(found_in) == 0
+    assert remember(L.ea_internal_generation()) == 1
+    ea.plan_cache_clear()
