@@ -1434,21 +1434,35 @@ int build_reduce(const ea_relation* const* ops, int n_in, int32_t join_op, int32
     len = std::max<int64_t>(ops[i]->shape[d.cd[i]], 2);
     a->nt = ops[i]->nb[d.cd[i]];
   }
-  // Lanes along a contiguous contracted letter, unless it is so short that
-  // most would idle.  Four wavefronts per output while one each leaves CUs
-  // idle; otherwise lanes along the output, and as many wavefronts per 64
-  // elements as it takes to have about 2000 of them, each with at least 8 terms.
-  a->rows = along && len >= 32;
+  // Lanes along a contiguous contracted letter (rows), a wavefront per output,
+  // or four where one each leaves CUs idle; else along the output, and as many
+  // wavefronts per 64 elements as it takes to have about 2000 of them, each
+  // with at least 8 terms.  A wavefront per output costs 0.4 ns an output (and
+  // 0.09 ns a tuple) whatever the length, lanes along the output 0.5 ns per 256
+  // terms: with many outputs rows win from about 200 terms on in blocks of 64
+  // or more.  us, f32, rows | lanes along the output:
+  //   2^20 x 64   416 | 129     2^20 x 256 in 64-blocks   627 | 693
+  //   2^20 x 128  428 | 279                in 32-blocks   948 | 698
+  //   2^20 x 256  427 | 564                in 4-blocks   5371 | 256
+  //   2^15 x 64  15.0 | 6.2     2^15 x 512  16.4 | 31     2^12 x 64  4.7 | 4.9
+  a->rows = along && len >= 32 && (outputs <= 12288 || (len >= 200 && len >= 64 * (int64_t)a->nt));
   a->rounds = 1;
   a->threads = 256;
   if (a->rows) {
     a->R = outputs < 4096 && len >= 256 ? 4 : 1;
   } else {
-    a->R = outputs >= 131072 || len < 32 ? 1 : outputs >= 32768 || len < 128 ? 4 : 16;
+    a->R = len < 32 || (outputs >= 131072 && !(along && a->nt == 1)) ? 1 : outputs >= 32768 || len < 128 ? 4 : 16;
     if (a->R == 16) a->threads = 1024;
-    if (a->R == 1 && outputs >= (int64_t(1) << 20)) a->rounds = 4;  // fewer, longer workgroups
   }
-  const int64_t per = a->threads / 64 / a->R * (a->rows ? 1 : 64) * a->rounds;
+  const int64_t once = a->threads / 64 / a->R * (a->rows ? 1 : 64);  // outputs of a workgroup per round
+  // Fewer, longer workgroups (and a shorter table) for many outputs, where
+  // rows are short (2^18 x 256 terms 108 ->
+  // 70 us, x 1024 180 -> 185).  And never so many workgroups that a launch would
+  // not hold them (2^32 threads).
+  if (a->rows ? outputs >= (int64_t(1) << 17) && len <= 768 : outputs >= int64_t(1) << 20)
+    a->rounds = 4;
+  while (outputs / (once * a->rounds) + C->nblocks > int64_t(1) << 23) a->rounds *= 2;
+  const int64_t per = once * a->rounds;
   std::vector<RedWork> work;
   for (int64_t b = 0; b < C->nblocks; ++b) {
     int64_t n = 1;

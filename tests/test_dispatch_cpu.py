@@ -54,3 +54,25 @@ def test_a_plan_cleared_meanwhile_is_not_recognised():
     assert remember(found_in) == 0
     assert remember(L.ea_internal_generation()) == 1
     ea.plan_cache_clear()
+
+
+SUM, MAX, NONE = ea.AGG_SUM, ea.AGG_MAX, ea.AGG_NONE
+
+
+@pytest.mark.parametrize("i,j,jblock,rows", [
+    (1 << 20, 64, 64, 0), (1 << 20, 128, 128, 0), (1 << 20, 256, 256, 1), (1 << 20, 256, 32, 0), (1 << 20, 256, 4, 0),
+    (1 << 20, 256, 64, 1), (32768, 64, 64, 0), (32768, 512, 512, 1), (4096, 64, 64, 1), (4096, 2048, 8, 1), (4096, 31, 31, 0),
+])
+def test_reduction_lanes(i, j, jblock, rows):
+    # a wavefront per output or lanes along the output, whichever measured
+    # faster (up to 20 times, with many outputs and short blocks)
+    d = _product("ij->i", dict(i=i, j=j), dict(j=jblock), "f32", agg=SUM)
+    assert (d["kind"], d["rows"]) == ("reduce", rows)
+
+
+@pytest.mark.parametrize("i,j,dtype", [(1 << 24, 32, "f32"), (1 << 24, 200, "bf16"), (70_000_000, 256, "bf16"),
+                                       (70_000_000, 40, "bf16")])
+def test_reduction_tables_and_launches_stay_small(i, j, dtype):
+    d = _product("ij->i", dict(i=i, j=j), dict(i=1 << 20), dtype, agg=SUM)
+    assert d["work"] * d["threads"] < 1 << 32  # what a launch holds
+    assert d["table_bytes"] <= i * j * ea.ELEM_SIZE[dtype] // 64  # of the input's bytes

@@ -91,3 +91,17 @@ def test_infinities_nan_and_signed_zeros():
     ea.joinagg("ij->ji", ea.JOIN_MUL, ea.AGG_NONE, [X], Y)  # a transpose keeps every bit
     torch.cuda.synchronize()
     assert Y.bytes().cpu().numpy().tobytes() == np.ascontiguousarray(x.T).tobytes()
+
+
+# several rows per wavefront; four wavefronts per 64 rows, once and several times over
+@pytest.mark.parametrize("i,j", [(131077, 203), (20001, 70), (1048583, 33)])
+def test_many_rows(i, j):
+    x = synth.integers((i, j), 5, -3, 3, "bf16")
+    pi = [0, i // 3, i // 3 + 1, i]
+    for part in ([0, j], [0, j // 2, j]):
+        X, S, M = upload(x, "bf16", [pi, part]), empty((i,), "f32", [pi]), empty((i,), "f32", [pi])
+        ea.joinagg("ij->i", ea.JOIN_MUL, ea.AGG_SUM, [X], S)
+        ea.joinagg("ij->i", ea.JOIN_MUL, ea.AGG_MAX, [X], M)
+        ref = synth.to_f64(x, "bf16")
+        np.testing.assert_array_equal(values(S), ref.sum(1))
+        np.testing.assert_array_equal(values(M), ref.max(1))
