@@ -588,7 +588,8 @@ bool contraction_ok(const Spec& sp, const ea_relation* const* ops, ContractDims*
 
 // An einsum that the reduction kernel takes: one or two inputs of one dtype, at
 // most one contracted letter and kRedRank output letters, 32-bit byte offsets
-// inside blocks, and a bounded table of tuples.
+// inside blocks, a bounded table of tuples, and a contracted letter or blocks of
+// some size.
 constexpr int64_t kRedMaxTuples = int64_t(1) << 22;
 bool reduction_ok(const Spec& sp, const ea_relation* const* ops, ReduceDims* d) {
   const int out = sp.n_in;
@@ -617,6 +618,11 @@ bool reduction_ok(const Spec& sp, const ea_relation* const* ops, ReduceDims* d) 
       d->cd[i] = x;
     }
   }
+  // elementwise joins over blocks of a few elements: the general kernel's single
+  // pass over them is shorter (transpose of 2048^2 in 8 x 8 blocks: 60 us for 71)
+  int64_t outputs = 1;
+  for (int x = 0; x < sp.rank[out]; ++x) outputs *= ops[out]->shape[x];
+  if (!contracted && outputs < 128 * ops[out]->nblocks) return false;
   return tuples <= kRedMaxTuples;
 }
 
@@ -1455,12 +1461,13 @@ int build_reduce(const ea_relation* const* ops, int n_in, int32_t join_op, int32
     if (a->R == 16) a->threads = 1024;
   }
   const int64_t once = a->threads / 64 / a->R * (a->rows ? 1 : 64);  // outputs of a workgroup per round
-  // Fewer, longer workgroups (and a shorter table) for many outputs, where
-  // rows are short (2^18 x 256 terms 108 ->
+  // Fewer, longer workgroups (and a shorter table) for many outputs, as far as
+  // the blocks fill them (4 rounds over blocks of 16 elements, 2^20 of them in
+  // all, took 168 us for 74 in one) and rows are short (2^18 x 256 terms 108 ->
   // 70 us, x 1024 180 -> 185).  And never so many workgroups that a launch would
   // not hold them (2^32 threads).
   if (a->rows ? outputs >= (int64_t(1) << 17) && len <= 768 : outputs >= int64_t(1) << 20)
-    a->rounds = 4;
+    a->rounds = (int32_t)std::max<int64_t>(1, std::min<int64_t>(4, outputs / C->nblocks / once));
   while (outputs / (once * a->rounds) + C->nblocks > int64_t(1) << 23) a->rounds *= 2;
   const int64_t per = once * a->rounds;
   std::vector<RedWork> work;

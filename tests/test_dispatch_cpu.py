@@ -70,6 +70,14 @@ def test_reduction_lanes(i, j, jblock, rows):
     assert (d["kind"], d["rows"]) == ("reduce", rows)
 
 
+@pytest.mark.parametrize("block,kind,rounds", [(4, "generic", None), (8, "generic", None), (16, "reduce", 1),
+                                               (32, "reduce", 4), (512, "reduce", 4)])
+@pytest.mark.parametrize("spec", ["ij->ji", "ij,ij->ij"])
+def test_elementwise_rounds_follow_the_blocks(spec, block, kind, rounds):
+    d = _product(spec, dict(i=2048, j=2048), block, "f32", agg=NONE)
+    assert d["kind"] == kind and d.get("rounds") == rounds
+
+
 @pytest.mark.parametrize("i,j,dtype", [(1 << 24, 32, "f32"), (1 << 24, 200, "bf16"), (70_000_000, 256, "bf16"),
                                        (70_000_000, 40, "bf16")])
 def test_reduction_tables_and_launches_stay_small(i, j, dtype):
