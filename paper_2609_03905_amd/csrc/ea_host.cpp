@@ -532,8 +532,8 @@ int64_t contract_tiles(const ea_relation* c, const ContractDims& d, int ts) {
 
 // A two-operand product that the contraction kernels take: both inputs of one
 // dtype; one letter in both and not in the output; every other letter in
-// exactly one input and the output (at most one per input), or in all three
-// (at most kConMaxBatch).  A is the operand without the output's last letter
+// exactly one input and the output (at most one per input, at least one in
+// all), or in all three (at most kConMaxBatch).  A is the operand without the output's last letter
 // where there is a choice, so that stores run along memory (a product of two
 // floats does not depend on their order).
 bool contraction_ok(const Spec& sp, const ea_relation* const* ops, ContractDims* d) {
@@ -579,7 +579,7 @@ bool contraction_ok(const Spec& sp, const ea_relation* const* ops, ContractDims*
     d->cn = z;
   }
   for (int i = n_batch; i < kConMaxBatch; ++i) d->ab[i] = d->bb[i] = d->cb[i] = -1;
-  if (d->ak < 0) return false;
+  if (d->ak < 0 || (d->am < 0 && d->bn < 0)) return false;
   // a bounded work list (one record per tile and batch index)
   int64_t work = contract_tiles(ops[2], *d, 64);
   for (int i = 0; i < n_batch && work <= kConMaxWork; ++i) work *= ops[2]->shape[d->cb[i]];
@@ -624,6 +624,90 @@ bool reduction_ok(const Spec& sp, const ea_relation* const* ops, ReduceDims* d) 
   for (int x = 0; x < sp.rank[out]; ++x) outputs *= ops[out]->shape[x];
   if (!contracted && outputs < 128 * ops[out]->nblocks) return false;
   return tuples <= kRedMaxTuples;
+}
+
+// Output tile of a contraction plan: the cheapest under a time model (us) of
+// the three kernels, fitted to fp32 products on one card (measured | model):
+//                            16 x 16      32 x 32      64 x 64
+//   256 x 256 x 256         3.7 |  3.5   5.8 |  7.0  10.7 | 10.6
+//   512 x 512 x 512         9.7 | 11     8.5 |  9.1  16.1 | 16.2
+//   512 x 2048 x 512       27.1 | 32    23.0 | 21    51.4 | 50
+//   768 x 768 x 768        24.5 | 30    21.0 | 21    23.0 | 22
+//   1024 x 128 x 1024      30.6 | 16    17.6 | 14     7.8 |  7.8
+//   1024 x 1024 x 1024     53.7 | 66    35.1 | 42    30.6 | 27
+//   2048 x 2048 x 2048      503 | 490    301 | 292    150 | 171
+//   65536 of 16 x 2 x 16                              473 | 415
+// The small tiles pay per k value of a tile (operand loads) and per tile; they
+// win while the 64 x 64 tiles are too few for the 256 CUs, whose cost is per
+// 32-deep step.  An operand read along k without vectors (block extents not
+// multiples of four) scatters a load of the small tiles over as many cache
+// lines as rows: 3 times the cost (72 tiles of 12 x 101 x 77 x 133: 13.5 us
+// with 32 x 32 tiles against 9.4 us with 64 x 64).
+struct ContractChoice {
+  int tile = 0;
+  double us = 0.0;
+  int n_batch = 0;
+  int rmaj_a = 0, rmaj_b = 0, vec_a = 0, vec_b = 0;  // see ContractArgs
+  int64_t steps = 0;                                 // 32-deep steps of a group's walk
+};
+ContractChoice contract_choice(const ea_relation* const* ops, const ContractDims& d) {
+  const ea_relation *A = ops[d.a_op], *B = ops[1 - d.a_op], *C = ops[2];
+  ContractChoice c;
+  int64_t batch = 1;
+  for (int i = 0; i < kConMaxBatch && d.ab[i] >= 0; ++i) {
+    ++c.n_batch;
+    batch *= C->shape[d.cb[i]];
+  }
+  // contiguous letter: the row (column) letter when it is the operand's last,
+  // else the contracted one is read along k; vectors of four when the
+  // contiguous letter's block extents are multiples of four (every other
+  // stride is then one too, and blocks start at 256-byte multiples)
+  auto last_ok = [](const ea_relation* r, int dim) {
+    if (dim != r->rank - 1) return false;
+    for (int64_t v : r->splits[dim])
+      if (v % 4) return false;
+    return true;
+  };
+  c.rmaj_a = d.am == A->rank - 1;
+  c.rmaj_b = d.bn == B->rank - 1;
+  c.vec_a = last_ok(A, A->rank - 1) && (c.rmaj_a || d.ak == A->rank - 1);
+  c.vec_b = last_ok(B, B->rank - 1) && (c.rmaj_b || d.bk == B->rank - 1);
+  const std::vector<int64_t>& ks = A->splits[d.ak];
+  for (int t = 0; t < A->nb[d.ak]; ++t) c.steps += (ks[t + 1] - ks[t] + 31) / 32;
+  const double K = (double)A->shape[d.ak];
+  // operands read along k without vectors: 0, 1 or 2
+  const double load = 1.0 + (!c.rmaj_a && !c.vec_a) + (!c.rmaj_b && !c.vec_b);
+  auto share = [&](int ts) { return (double)(contract_tiles(C, d, ts) * batch) / 256.0; };
+  const double c16 = 2.2 + load * std::max(1.0, share(16)) * (0.4 + 3.5e-3 * K);
+  const double c32 = 3.5 + load * std::max(1.0, share(32)) * (1.5 + 8.0e-3 * K);
+  const double s64 = share(64);
+  // (several tiles per CU: an odd count of steps ends with one of zeros, and a
+  // single step waits for its loads)
+  const double c64 = 5.0 + (s64 <= 1.0 ? 0.7 * (double)c.steps
+                                       : std::ceil(s64) * (0.65 * (double)(c.steps + (c.steps & 1)) + (c.steps == 1 ? 0.3 : 0.0)));
+  c.us = std::min(c64, std::min(c32, c16));
+  c.tile = c64 <= c32 && c64 <= c16 ? 64 : c32 <= c16 ? 32 : 16;
+  return c;
+}
+
+// Whether reduce_kernel is estimated faster for a contraction that it takes
+// too, with a margin for two coarse models: where few of a tile's outputs exist
+// (many small products, products with a vector) it reads an operand value per
+// term, about 3 ps each, and the tiles their whole rows and columns.  us, f32,
+// contraction | reduction (model), and the general kernel that took these calls
+// before either:
+//   524288 of 2 x 8 x 2            534 |  23 (876 |  54)   107
+//   65536 of 4 x 1 x 64            457 |  51 (413 |  54)   202
+//   65536 of 16 x 2 x 16           473 |  56 (210 | 104)   289
+//   2^20 x 4 by a vector           101 | 7.6 (106 |  16)    26
+//   2^20 x 16 by a vector          103 |  34 (107 |  54)    85
+//   32768 of 4 x 256 x 1            80 | 122 (166 | 104)   435
+//   20000 of 16 x 16 x 16           26 |  36 ( 38 | 249)   470
+//   4096 x 4096 by a vector       13.4 |  15 ( 17 |  54)  3618
+bool reduction_faster(const ea_relation* const* ops, const ContractDims& d) {
+  double terms = (double)ops[d.a_op]->shape[d.ak];
+  for (int x = 0; x < ops[2]->rank; ++x) terms *= (double)ops[2]->shape[x];
+  return 3.5 + 3.0e-6 * terms < 0.6 * contract_choice(ops, d).us;
 }
 
 bool is_float_dtype(int32_t dt) { return dt == EA_F32 || dt == EA_BF16 || dt == EA_F16; }
@@ -681,8 +765,11 @@ int classify(const Spec& sp, int32_t join_op, int32_t agg_op, const ea_relation*
           }
         }
       }
-      if (join_op == EA_JOIN_MUL && agg_op == EA_AGG_SUM && contraction_ok(sp, ops, &oi->con)) oi->kind = K_CONTRACT;
-      else if (reduction_ok(sp, ops, &oi->red)) oi->kind = K_REDUCE;
+      const bool reduce = reduction_ok(sp, ops, &oi->red);
+      if (reduce) oi->kind = K_REDUCE;
+      if (join_op == EA_JOIN_MUL && agg_op == EA_AGG_SUM && contraction_ok(sp, ops, &oi->con) &&
+          !(reduce && reduction_faster(ops, oi->con)))
+        oi->kind = K_CONTRACT;
       return EA_OK;
     }
     case EA_OP_SWIGLU: {
@@ -1236,62 +1323,22 @@ GemmDlPlan gemm_units_dl(const ea_relation* a, const ea_relation* c, int tn, int
   return bal_cost < ev_cost ? bal : ev;
 }
 
-// Output tile of a contraction plan: the cheapest under a time model (us) of
-// the three kernels, fitted to fp32 products on one card (measured | model):
-//                            16 x 16      32 x 32      64 x 64
-//   256 x 256 x 256         3.7 |  3.5   5.8 |  7.0  10.7 | 10.6
-//   512 x 512 x 512         9.7 | 11     8.5 |  9.1  16.1 | 16.2
-//   512 x 2048 x 512       27.1 | 32    23.0 | 21    51.4 | 50
-//   768 x 768 x 768        24.5 | 30    21.0 | 21    23.0 | 22
-//   1024 x 128 x 1024      30.6 | 16    17.6 | 14     7.8 |  7.8
-//   1024 x 1024 x 1024     53.7 | 66    35.1 | 42    30.6 | 27
-//   2048 x 2048 x 2048      503 | 490    301 | 292    150 | 171
-// The small tiles pay per k value of a tile (operand loads) and per tile; they
-// win while the 64 x 64 tiles are too few for the 256 CUs, whose cost is per
-// 32-deep step.  An operand read along k without vectors (block extents not
-// multiples of four) scatters a load of the small tiles over as many cache
-// lines as rows: 3 times the cost (72 tiles of 12 x 101 x 77 x 133: 13.5 us
-// with 32 x 32 tiles against 9.4 us with 64 x 64).
-int contract_tile(const ea_relation* c, const ContractDims& d, int64_t batch, int64_t K, int64_t steps, int scattered) {
-  const double load = 1.0 + scattered;  // operands read along k without vectors: 0, 1 or 2
-  auto share = [&](int ts) { return (double)(contract_tiles(c, d, ts) * batch) / 256.0; };
-  const double c16 = 2.2 + load * std::max(1.0, share(16)) * (0.4 + 3.5e-3 * (double)K);
-  const double c32 = 3.5 + load * std::max(1.0, share(32)) * (1.5 + 8.0e-3 * (double)K);
-  const double s64 = share(64);
-  const double c64 = 5.0 + (double)steps * (s64 <= 1.0 ? 0.7 : 0.65 * std::ceil(s64));
-  if (c64 <= c32 && c64 <= c16) return 64;
-  return c32 <= c16 ? 32 : 16;
-}
-
 int build_contract(const ea_relation* const* ops, const ContractDims& d, int64_t tuple_cap, Image* img, Extra* ex,
                    ContractArgs* a) {
-  const ea_relation *A = ops[d.a_op], *B = ops[1 - d.a_op], *C = ops[2];
+  const ea_relation *A = ops[d.a_op], *C = ops[2];
+  const ContractChoice c = contract_choice(ops, d);
   memset(a, 0, sizeof(*a));
-  int64_t batch = 1;
-  for (int i = 0; i < kConMaxBatch && d.ab[i] >= 0; ++i) {
-    ++a->n_batch;
-    batch *= C->shape[d.cb[i]];
-  }
+  a->n_batch = c.n_batch;
   a->dt_in = A->dtype;
   a->dt_out = C->dtype;
   a->nt = A->nb[d.ak];
-  // contiguous letter: the row (column) letter when it is the operand's last,
-  // else the contracted one is read along k; vectors of four when the
-  // contiguous letter's block extents are multiples of four (every other
-  // stride is then one too, and blocks start at 256-byte multiples)
-  auto last_ok = [](const ea_relation* r, int dim) {
-    if (dim != r->rank - 1) return false;
-    for (int64_t v : r->splits[dim])
-      if (v % 4) return false;
-    return true;
-  };
-  a->rmaj_a = d.am == A->rank - 1;
-  a->rmaj_b = d.bn == B->rank - 1;
-  a->vec_a = last_ok(A, A->rank - 1) && (a->rmaj_a || d.ak == A->rank - 1);
-  a->vec_b = last_ok(B, B->rank - 1) && (a->rmaj_b || d.bk == B->rank - 1);
+  a->rmaj_a = c.rmaj_a;
+  a->rmaj_b = c.rmaj_b;
+  a->vec_a = c.vec_a;
+  a->vec_b = c.vec_b;
+  a->n_steps = (int32_t)c.steps;
+  a->tile = c.tile;
   const std::vector<int64_t>& ks = A->splits[d.ak];
-  for (int t = 0; t < a->nt; ++t) a->n_steps += (int32_t)((ks[t + 1] - ks[t] + 31) / 32);
-  a->tile = contract_tile(C, d, batch, A->shape[d.ak], a->n_steps, (!a->rmaj_a && !a->vec_a) + (!a->rmaj_b && !a->vec_b));
   if (a->tile < 64) {
     const int kg = 256 / a->tile;  // k values per group (four MFMAs)
     std::vector<int64_t> pre(1, 0);

@@ -84,3 +84,19 @@ def test_reduction_tables_and_launches_stay_small(i, j, dtype):
     d = _product("ij->i", dict(i=i, j=j), dict(i=1 << 20), dtype, agg=SUM)
     assert d["work"] * d["threads"] < 1 << 32  # what a launch holds
     assert d["table_bytes"] <= i * j * ea.ELEM_SIZE[dtype] // 64  # of the input's bytes
+
+
+@pytest.mark.parametrize("spec,ext,kind", [
+    # no row and no column letter, many small products, products with a vector
+    ("ij,ij->i", dict(i=131072, j=64), "reduce"), ("ij,ij->i", dict(i=1 << 20, j=4), "reduce"),
+    ("ij,ij->j", dict(i=64, j=131072), "reduce"), ("ij,ij->i", dict(i=3, j=5), "reduce"),
+    ("bij,bjk->bik", dict(b=524288, i=2, j=8, k=2), "reduce"), ("bij,bjk->bik", dict(b=65536, i=16, j=2, k=16), "reduce"),
+    ("bij,bjk->bik", dict(b=65536, i=4, j=1, k=64), "reduce"), ("ij,j->i", dict(i=1 << 20, j=4), "reduce"),
+    ("ij,j->i", dict(i=100, j=8192), "reduce"), ("ij,i->j", dict(i=16, j=1 << 20), "reduce"),
+    # matrix products of any size
+    ("ij,jk->ik", dict(i=33, j=33, k=33), "contract"), ("ij,jk->ik", dict(i=4096, j=1, k=4096), "contract"),
+    ("hqd,hkd->hqk", dict(h=8, q=256, k=256, d=128), "contract"), ("bij,bjk->bik", dict(b=20000, i=16, j=16, k=16), "contract"),
+    ("hqd,hkd->hqk", dict(h=4096, q=1, k=256, d=128), "contract"), ("ij,j->i", dict(i=4096, j=4096), "contract"),
+])
+def test_contraction_or_reduction(spec, ext, kind):
+    assert _product(spec, ext, 1 << 30, "f32")["kind"] == kind

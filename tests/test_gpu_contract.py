@@ -13,7 +13,7 @@ import pytest
 
 import oracle
 import synth
-from helpers import assert_close, empty, expected, upload, values
+from helpers import assert_close, describe, empty, expected, upload, values
 from paper_2609_03905_amd import ea
 
 pytestmark = pytest.mark.gpu
@@ -53,9 +53,8 @@ def test_contract_letter_orders(spec, dtype):
 
 
 @pytest.mark.parametrize("i,j,k", [
-    (1, 1, 1), (16, 4, 16), (17, 3, 15), (64, 128, 64), (65, 260, 130),  # 16 x 16 tiles
-    (512, 96, 448), (500, 100, 444),                                     # 32 x 32 tiles
-    (1024, 64, 1024), (1000, 36, 1060), (1031, 33, 1025),                # 64 x 64 tiles
+    (1, 1, 1), (16, 4, 16), (17, 3, 15), (64, 128, 64), (65, 260, 130), (512, 96, 448), (500, 100, 444),
+    (1024, 64, 1024), (1000, 36, 1060), (1031, 33, 1025),
 ])
 @pytest.mark.parametrize("spec", ["ij,jk->ik", "ij,kj->ik", "ji,jk->ik"])
 def test_contract_tiles(spec, i, j, k):
@@ -83,3 +82,25 @@ def test_contract_non_finite_inputs_stay_in_their_rows(n):
     np.testing.assert_array_equal(np.isposinf(got), np.isposinf(ref))
     ok = np.isfinite(ref)
     assert_close(got[ok], ref[ok], rel_fro=1e-5, what="finite part")
+
+
+@pytest.mark.parametrize("i,j,k,tile", [
+    (64, 128, 64, 16), (65, 131, 40, 16),      # vectors; element loads along j, odd rows
+    (512, 512, 512, 32), (516, 1000, 444, 32), (600, 300, 517, 32),
+    (1024, 64, 1024, 64), (1031, 33, 1025, 64), (1030, 70, 1100, 64),
+])
+@pytest.mark.parametrize("spec", ["ij,jk->ik", "ij,kj->ik", "ji,jk->ik", "ji,kj->ik"])
+def test_contract_every_tile(spec, i, j, k, tile):
+    # the sizes' tiles are what the plans take (two blocks along j)
+    ext, part = dict(i=i, j=j, k=k), dict(i=[0, i], j=[0, j // 8 * 4, j], k=[0, k])
+    lhs, rhs = spec.split("->")
+    shape, parts = (lambda s: tuple(ext[x] for x in s)), (lambda s: [part[x] for x in s])
+    ops = [(shape(s), "f32", parts(s)) for s in lhs.split(",") + [rhs]]
+    assert describe(spec, ea.JOIN_MUL, ea.AGG_SUM, ops)["tile"] == tile
+    xs = [synth.normal(s, 40 + n, dtype="f32") for n, (s, _, _) in enumerate(ops[:2])]
+    ins = [upload(x, "f32", p) for x, (_, _, p) in zip(xs, ops)]
+    C = empty((i, k), "f32", parts(rhs))
+    ea.joinagg(spec, ea.JOIN_MUL, ea.AGG_SUM, ins, C)
+    a, b = (synth.to_f64(x, "f32") for x in xs)
+    assert_close(values(C), (a if spec[0] == "i" else a.T) @ (b if spec[3] == "j" else b.T), rel_fro=1e-5,
+                 what=f"{spec} {i} {j} {k}")

@@ -14,7 +14,7 @@ import torch
 
 import oracle
 import synth
-from helpers import assert_close, empty, expected, upload, values
+from helpers import assert_close, describe, empty, expected, upload, values
 from paper_2609_03905_amd import ea
 
 pytestmark = pytest.mark.gpu
@@ -105,3 +105,18 @@ def test_many_rows(i, j):
         ref = synth.to_f64(x, "bf16")
         np.testing.assert_array_equal(values(S), ref.sum(1))
         np.testing.assert_array_equal(values(M), ref.max(1))
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
+@pytest.mark.parametrize("spec,ext", [
+    ("ij,ij->i", dict(i=37, j=45)), ("ij,ij->j", dict(i=37, j=45)), ("bji,ijb->bi", dict(b=3, i=70, j=33)),
+    ("ij,ij->i", dict(i=300, j=513)), ("bij,bjk->bik", dict(b=3000, i=2, j=3, k=2)), ("ij,j->i", dict(i=20000, j=3)),
+])
+def test_sums_of_products_that_no_tile_serves(spec, ext, dtype):
+    # no row and no column letter, many small products, products with a vector
+    part = {x: synth.splits(n, n) for x, n in ext.items()}
+    ops = [(tuple(ext[x] for x in s), dtype, [part[x] for x in s]) for s in spec.replace("->", ",").split(",")]
+    assert describe(spec, ea.JOIN_MUL, ea.AGG_SUM, ops)["kind"] == "reduce"
+    for nblocks in (1, 3):
+        got, ref = _run(spec, "mul", "sum", ext, nblocks if min(ext.values()) >= nblocks else 1, dtype, integers=True)
+        np.testing.assert_array_equal(got, ref)
