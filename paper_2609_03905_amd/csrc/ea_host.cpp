@@ -642,7 +642,12 @@ bool reduction_ok(const Spec& sp, const ea_relation* const* ops, ReduceDims* d) 
 // 32-deep step.  An operand read along k without vectors (block extents not
 // multiples of four) scatters a load of the small tiles over as many cache
 // lines as rows: 3 times the cost (72 tiles of 12 x 101 x 77 x 133: 13.5 us
-// with 32 x 32 tiles against 9.4 us with 64 x 64).
+// with 32 x 32 tiles against 9.4 us with 64 x 64).  Both read so ("ij,kj->ik"
+// with odd j), measured | model:
+//   174 x 65 x 758         11.9 |  11   9.4 |  9.6   9.1 |  8.6
+//   174 x 163 x 758        15.5 |  14  11.6 | 11.9  11.7 | 12.2
+//   500 x 1001 x 500       51.0 |  52  27.0 |  32   43.9 | 43
+//   1000 x 1001 x 300      63.1 |  65  54.1 |  60   43.0 | 43
 struct ContractChoice {
   int tile = 0;
   double us = 0.0;
@@ -675,15 +680,19 @@ ContractChoice contract_choice(const ea_relation* const* ops, const ContractDims
   const std::vector<int64_t>& ks = A->splits[d.ak];
   for (int t = 0; t < A->nb[d.ak]; ++t) c.steps += (ks[t + 1] - ks[t] + 31) / 32;
   const double K = (double)A->shape[d.ak];
-  // operands read along k without vectors: 0, 1 or 2
-  const double load = 1.0 + (!c.rmaj_a && !c.vec_a) + (!c.rmaj_b && !c.vec_b);
-  auto share = [&](int ts) { return (double)(contract_tiles(C, d, ts) * batch) / 256.0; };
-  const double c16 = 2.2 + load * std::max(1.0, share(16)) * (0.4 + 3.5e-3 * K);
-  const double c32 = 3.5 + load * std::max(1.0, share(32)) * (1.5 + 8.0e-3 * K);
-  const double s64 = share(64);
+  const int scattered = (!c.rmaj_a && !c.vec_a) + (!c.rmaj_b && !c.vec_b);  // operands read along k without vectors
+  const double load = 1.0 + scattered;
+  // tiles per CU; with both operands scattered a CU's last tile costs like a whole round
+  auto share = [&](int ts) {
+    const double n = std::max(1.0, (double)(contract_tiles(C, d, ts) * batch) / 256.0);
+    return scattered == 2 ? std::ceil(n) : n;
+  };
+  const double c16 = 2.2 + (scattered == 2 && share(16) > 1.0 ? std::min(3.0, 0.045 * K) : 0.0) + load * share(16) * (0.4 + 3.5e-3 * K);
+  const double c32 = 3.5 + load * share(32) * (1.5 + 8.0e-3 * K);
+  const double s64 = (double)(contract_tiles(C, d, 64) * batch) / 256.0;
   // (several tiles per CU: an odd count of steps ends with one of zeros, and a
   // single step waits for its loads)
-  const double c64 = 5.0 + (s64 <= 1.0 ? 0.7 * (double)c.steps
+  const double c64 = 5.0 + (s64 <= 1.0 ? (scattered == 2 ? 1.2 : 0.7) * (double)c.steps
                                        : std::ceil(s64) * (0.65 * (double)(c.steps + (c.steps & 1)) + (c.steps == 1 ? 0.3 : 0.0)));
   c.us = std::min(c64, std::min(c32, c16));
   c.tile = c64 <= c32 && c64 <= c16 ? 64 : c32 <= c16 ? 32 : 16;

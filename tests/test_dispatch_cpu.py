@@ -100,3 +100,12 @@ def test_reduction_tables_and_launches_stay_small(i, j, dtype):
 ])
 def test_contraction_or_reduction(spec, ext, kind):
     assert _product(spec, ext, 1 << 30, "f32")["kind"] == kind
+
+
+@pytest.mark.parametrize("i,j,k,tile", [
+    (174, 65, 758, 64), (174, 163, 758, 32), (500, 1001, 500, 32), (1000, 1001, 300, 64), (300, 401, 300, 16), (75, 9, 1116, 16),
+    (512, 512, 512, 32), (256, 256, 256, 16), (1024, 128, 1024, 64),
+])
+def test_contraction_tiles_read_along_k(i, j, k, tile):
+    # odd j: every load of a small tile touches as many cache lines as rows
+    assert _product("ij,kj->ik", dict(i=i, j=j, k=k), 1 << 30, "f32")["tile"] == tile
