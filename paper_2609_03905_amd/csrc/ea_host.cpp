@@ -297,7 +297,7 @@ struct Image {
   size_t put_vec(const std::vector<T>& v) { return put(v.data(), v.size() * sizeof(T)); }
 };
 
-enum Kind { K_GENERIC = 1, K_GEMM, K_CONTRACT, K_REDUCE, K_RMSNORM, K_SOFTMAX, K_ATTENTION, K_REPART };
+enum Kind { K_GENERIC = 1, K_GEMM, K_GEMM32, K_CONTRACT, K_REDUCE, K_RMSNORM, K_SOFTMAX, K_ATTENTION, K_REPART };
 
 // row-reduction plan constants (see RowArgs)
 struct RowLayout {
@@ -518,7 +518,7 @@ int64_t max_block_bytes(const ea_relation* r) {
 }
 
 // ts x ts tiles of every output block of a contraction (per batch index)
-constexpr int64_t kConMaxWork = int64_t(1) << 20;
+constexpr int64_t kConMaxWork = int64_t(1) << 20, kConMaxTiles = int64_t(1) << 23;
 int64_t contract_tiles(const ea_relation* c, const ContractDims& d, int ts) {
   int64_t n = 1;
   for (int dim : {d.cm, d.cn}) {
@@ -580,10 +580,12 @@ bool contraction_ok(const Spec& sp, const ea_relation* const* ops, ContractDims*
   }
   for (int i = n_batch; i < kConMaxBatch; ++i) d->ab[i] = d->bb[i] = d->cb[i] = -1;
   if (d->ak < 0 || (d->am < 0 && d->bn < 0)) return false;
-  // a bounded work list (one record per tile and batch index)
-  int64_t work = contract_tiles(ops[2], *d, 64);
-  for (int i = 0; i < n_batch && work <= kConMaxWork; ++i) work *= ops[2]->shape[d->cb[i]];
-  return work <= kConMaxWork;
+  // a bounded work list (one record per tile and batch index), larger only where
+  // every record stands for a tile of 1024 outputs or more
+  int64_t work = contract_tiles(ops[2], *d, 64), outputs = 1;
+  for (int i = 0; i < n_batch && work <= kConMaxTiles; ++i) work *= ops[2]->shape[d->cb[i]];
+  for (int x = 0; x < ops[2]->rank; ++x) outputs *= ops[2]->shape[x];
+  return work <= kConMaxWork || (work <= kConMaxTiles && work <= outputs / 1024);
 }
 
 // An einsum that the reduction kernel takes: one or two inputs of one dtype, at
@@ -776,9 +778,25 @@ int classify(const Spec& sp, int32_t join_op, int32_t agg_op, const ea_relation*
       }
       const bool reduce = reduction_ok(sp, ops, &oi->red);
       if (reduce) oi->kind = K_REDUCE;
-      if (join_op == EA_JOIN_MUL && agg_op == EA_AGG_SUM && contraction_ok(sp, ops, &oi->con) &&
-          !(reduce && reduction_faster(ops, oi->con)))
-        oi->kind = K_CONTRACT;
+      if (join_op != EA_JOIN_MUL || agg_op != EA_AGG_SUM) return EA_OK;
+      if (contraction_ok(sp, ops, &oi->con)) {
+        if (!(reduce && reduction_faster(ops, oi->con))) oi->kind = K_CONTRACT;
+      } else if (n_in == 2 && sp.rank[0] == 2 && sp.rank[1] == 2 && sp.rank[2] == 2 && ops[0]->dtype == EA_F32 &&
+                 ops[1]->dtype == EA_F32 && !(prm && prm->residual)) {
+        // fp32 block products beyond the contraction kernels' offsets or work
+        // list: the vector-ALU kernel with 64-bit indexes
+        const char a = sp.let[0][0], b = sp.let[0][1];
+        const char* L1 = sp.let[1];
+        const char* L2 = sp.let[2];
+        int kmaj = -1;
+        char c = 0;
+        if (L1[0] == b && L1[1] != a && L1[1] != b) { kmaj = 0; c = L1[1]; }
+        else if (L1[1] == b && L1[0] != a && L1[0] != b) { kmaj = 1; c = L1[0]; }
+        if (kmaj >= 0 && L2[0] == a && L2[1] == c) {
+          oi->kind = K_GEMM32;
+          oi->b_kmajor = kmaj;
+        }
+      }
       return EA_OK;
     }
     case EA_OP_SWIGLU: {
@@ -1843,6 +1861,22 @@ int plan_image(const Spec& sp, int32_t join_op, int32_t agg_op, const ea_relatio
       p->ws_partial_bytes = slots * slot_bytes;
       break;
     }
+    case K_GEMM32: {  // square tiles of every output block
+      std::vector<Gemm32Work> work;
+      const ea_relation* c = ops[sp.n_in];
+      int32_t co[kMaxRank];
+      for (int64_t b = 0; b < c->nblocks; ++b) {
+        block_coords(c, b, co);
+        const int64_t me = c->splits[0][co[0] + 1] - c->splits[0][co[0]];
+        const int64_t ne = c->splits[1][co[1] + 1] - c->splits[1][co[1]];
+        for (int64_t m0 = 0; m0 < me; m0 += kGemm32Tile)
+          for (int64_t n0 = 0; n0 < ne; n0 += kGemm32Tile)
+            work.push_back(Gemm32Work{(int32_t)b, (int32_t)m0, (int32_t)n0, 0});
+      }
+      ex->work = img->put_vec(work);
+      ex->n_work = (int64_t)work.size();
+      break;
+    }
     case K_REDUCE: e = build_reduce(ops, sp.n_in, join_op, agg_op, oi.red, p->tuple_cap, img, ex, &p->red); break;
     case K_CONTRACT: e = build_contract(ops, oi.con, p->tuple_cap, img, ex, &p->con); break;
     case K_RMSNORM:
@@ -2403,6 +2437,25 @@ int run_planned(const Call& call, int32_t join_op, int32_t n_in, const ea_relati
       EA_HIP_TRY(launch_gemm(a, s));
       break;
     }
+    case K_GEMM32: {
+      Gemm32Args a;
+      memset(&a, 0, sizeof(a));
+      a.tuples = plan->d_tuples;
+      a.goff = plan->d_goff;
+      a.blk_a = plan->d_blk[0];
+      a.blk_b = plan->d_blk[1];
+      a.blk_c = plan->d_blk[2];
+      a.a = (const char*)in[0]->data;
+      a.b = (const char*)in[1]->data;
+      a.c = (char*)out->data;
+      a.work = (const Gemm32Work*)plan->d_work;
+      a.n_work = plan->n_work;
+      a.tuple_stride = 3;
+      a.b_kmajor = plan->b_kmajor;
+      a.dt_out = out->dtype;
+      EA_HIP_TRY(launch_gemm32(a, s));
+      break;
+    }
     case K_REDUCE: {
       ReduceArgs a = plan->red;
       for (int i = 0; i < n_in; ++i) a.in[i] = (const char*)in[i]->data;
@@ -2783,6 +2836,7 @@ int ea_internal_describe(const char* spec, int32_t join_op, int32_t agg_op, int3
       t << "kind=gemm direct=" << p.gemm_direct << " tile_m=" << p.gemm_tm << " tile_n=" << p.gemm_tn
         << " tail=" << p.gemm_tail << " balanced=" << p.gemm_balanced << " by_class=" << p.gemm_by_class;
       break;
+    case K_GEMM32: t << "kind=gemm32"; break;
     case K_CONTRACT: t << "kind=contract tile=" << p.con.tile; break;
     case K_REDUCE:
       threads = p.red.threads;

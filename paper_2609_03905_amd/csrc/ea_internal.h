@@ -279,6 +279,33 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s);
 hipError_t launch_gemm_prep(const GemmArgs& a, GemmUnit* units, int64_t tuple_cap, hipStream_t s);
 
 // ---------------------------------------------------------------------------
+// fp32 block product "ab,bc->ac" / "ab,cb->ac" on the vector ALUs: a workgroup
+// owns a kGemm32Tile-square tile of one output block and sums its key's tuples.
+// ---------------------------------------------------------------------------
+constexpr int kGemm32Tile = 32;
+struct Gemm32Work {
+  int32_t block, m0, n0, pad;
+};
+
+struct Gemm32Args {
+  const int32_t* tuples;
+  const int32_t* goff;
+  const DevBlk* blk_a;
+  const DevBlk* blk_b;
+  const DevBlk* blk_c;
+  const char* a;
+  const char* b;
+  char* c;
+  const Gemm32Work* work;
+  int64_t n_work;
+  int32_t tuple_stride;
+  int32_t b_kmajor;  // 1: B blocks are [n][k] ("ab,cb->ac")
+  int32_t dt_out;    // EA_F32, EA_BF16 or EA_F16
+};
+
+hipError_t launch_gemm32(const Gemm32Args& a, hipStream_t s);
+
+// ---------------------------------------------------------------------------
 // Two-operand contraction on the fp32 matrix cores: one contracted letter, at
 // most one row letter (A, output), one column letter (B, output) and
 // kConMaxBatch batch letters (A, B, output), in any order.

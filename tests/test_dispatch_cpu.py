@@ -109,3 +109,14 @@ def test_contraction_or_reduction(spec, ext, kind):
 def test_contraction_tiles_read_along_k(i, j, k, tile):
     # odd j: every load of a small tile touches as many cache lines as rows
     assert _product("ij,kj->ik", dict(i=i, j=j, k=k), 1 << 30, "f32")["tile"] == tile
+
+
+@pytest.mark.parametrize("spec,ext,block,kind", [
+    ("ij,jk->ik", dict(i=40000, j=16000, k=64), 1 << 30, "gemm32"),  # an operand block of 2.4 GiB
+    ("ij,kj->ik", dict(i=64, j=16000, k=40000), 1 << 30, "gemm32"),
+    ("ij,jk->ik", dict(i=65536, j=64, k=65536), 1 << 30, "gemm32"),  # an output block of 2^32 elements
+    ("ij,jk->ik", dict(i=40000, j=13000, k=64), 1 << 30, "contract"),
+    ("ij,jk->ik", dict(i=131072, j=4096, k=65536), 4096, "contract"),  # 2^21 tiles of 64 x 64
+])
+def test_large_f32_products(spec, ext, block, kind):
+    assert _product(spec, ext, block, "f32")["kind"] == kind
