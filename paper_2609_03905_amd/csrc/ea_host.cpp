@@ -2842,8 +2842,23 @@ int ea_internal_describe(const char* spec, int32_t join_op, int32_t agg_op, int3
       threads = p.red.threads;
       t << "kind=reduce rows=" << p.red.rows << " share=" << p.red.R << " rounds=" << p.red.rounds;
       break;
-    case K_RMSNORM: t << "kind=rmsnorm"; break;
-    case K_SOFTMAX: t << "kind=softmax"; break;
+    case K_RMSNORM:
+    case K_SOFTMAX: {
+      RowArgs a;
+      memset(&a, 0, sizeof(a));
+      a.vec = p.rows.vec;
+      a.row_len = p.rows.row_len;
+      a.max_seg = p.rows.nseg;
+      a.dt_x = ops[0]->dtype;
+      a.n_rowtasks = (int32_t)p.n_work;
+      const RowsLaunch l = rows_launch(a, p.kind == K_SOFTMAX);
+      t << "kind=" << (p.kind == K_SOFTMAX ? "softmax" : "rmsnorm") << " path="
+        << (l.path == RowsLaunch::kVec ? "vec" : l.path == RowsLaunch::kElem ? "elem" : "scalar")
+        << " waves=" << l.waves << " per_lane=" << l.per_lane;
+      p.n_work = l.grid;
+      threads = l.threads;
+      break;
+    }
     case K_ATTENTION: t << "kind=attention"; break;
     default: t << "kind=other";
   }

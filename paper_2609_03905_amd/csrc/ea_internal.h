@@ -421,6 +421,16 @@ struct RowArgs {
 
 bool rows_vec_ok(int64_t row_len, int64_t max_segments, bool seg_aligned, int es);
 
+// How a row reduction is launched: the vector path, the element path with
+// `waves` wavefronts per row and `per_lane` elements each, or the scalar path.
+struct RowsLaunch {
+  enum Path { kScalar, kVec, kElem } path = kScalar;
+  int32_t waves = 1, per_lane = 0;
+  int64_t grid = 0;
+  int32_t threads = 0;
+};
+RowsLaunch rows_launch(const RowArgs& a, bool softmax);
+
 hipError_t launch_rmsnorm(const RowArgs& a, hipStream_t s);
 hipError_t launch_softmax(const RowArgs& a, hipStream_t s);
 

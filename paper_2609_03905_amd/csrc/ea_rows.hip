@@ -14,8 +14,8 @@
 //
 // Causal softmax skips the loads of keys after the row's query position and
 // stores zeros there.  Segments that are not 16-byte multiples take an element
-// path that also holds the row in registers; rows too long for registers a
-// scalar path that re-reads the row.
+// path that also holds the row in registers; rows too long for registers, and
+// some short ones (rows_launch), a scalar path that re-reads the row.
 #include <type_traits>
 
 #include "ea_device.h"
@@ -450,7 +450,17 @@ __global__ __launch_bounds__(kThreads * WPR) void rows_vec_kernel(RowArgs a) {
 // 32 elements per lane), sixteen beyond.  Sixteen wavefronts already above 2048
 // keep only two rows per CU in flight, each waiting for its table, its loads
 // and its barriers in turn (causal softmax 4 x 3092^2 bf16: 108 us against 54);
-// 64 elements per lane on one wavefront: 95 us.
+// 64 elements per lane on one wavefront: 95 us.  With more rows than fill the
+// GPU at four wavefronts each (4096), rows of up to 1024 elements take one
+// wavefront too: there the table and barriers of a row are what counts.  And
+// RMSNorm keeps the scalar path where its second read comes from the cache and
+// costs less than the table: up to 384 elements, and with many bf16 rows between
+// 1024 and 1500.  us, scalar | one wavefront | four:
+//   RMSNorm 32768 x 515 bf16    41 | 40 | 63    262144 x 33 bf16    75 | 83
+//           32768 x 769 bf16    57 | 54 | 76    32768 x 300 bf16  25.5 | 26.5
+//           32768 x 1031 bf16   73 | 86 | 89    32768 x 500 bf16  38.3 | 37.1
+//           4096 x 769 bf16   10.1 | 10.2 | 10.4   1024 x 769 bf16   8.2 | 8.6 | 5.1
+//   softmax 32768 x 700 bf16    59 | 39 | 61    32768 x 1030 bf16   85 | 83 | 75
 // Times, scalar path -> this: RMSNorm 1089 x 7041 f32 102 -> 21 us, 211 x 653
 // bf16 7.2 -> 4.5; causal softmax 4 x 3092^2 bf16 124 -> 54 us, softmax 2893^2
 // f32 68 -> 16 us.  Bound by its 2- and 4-byte accesses and the row's latency.
@@ -575,19 +585,18 @@ __global__ __launch_bounds__(W == 1 ? kThreads : 64 * W) void rows_elem_kernel(R
 }
 
 template <typename XT, bool SOFTMAX, int K, int W>
-void launch_elem_kw(const RowArgs& a, hipStream_t s) {
-  const uint32_t tasks = (uint32_t)a.n_rowtasks;
-  hipLaunchKernelGGL((rows_elem_kernel<XT, SOFTMAX, K, W>), dim3(W == 1 ? tasks : tasks * kRowsPerTask),
-                     dim3(W == 1 ? kThreads : 64 * W), 0, s, a);
+void launch_elem_kw(const RowArgs& a, const RowsLaunch& l, hipStream_t s) {
+  hipLaunchKernelGGL((rows_elem_kernel<XT, SOFTMAX, K, W>), dim3((uint32_t)l.grid), dim3(l.threads), 0, s, a);
 }
 template <typename XT, bool SOFTMAX>
-void launch_elem(const RowArgs& a, hipStream_t s) {
-  const int L = a.row_len;
-  if (L <= 512) launch_elem_kw<XT, SOFTMAX, 8, 1>(a, s);
-  else if (L <= 2048) launch_elem_kw<XT, SOFTMAX, 8, 4>(a, s);
-  else if (L <= 4096) launch_elem_kw<XT, SOFTMAX, 16, 4>(a, s);
-  else if (L <= 8192) launch_elem_kw<XT, SOFTMAX, 32, 4>(a, s);
-  else launch_elem_kw<XT, SOFTMAX, 16, 16>(a, s);
+void launch_elem(const RowArgs& a, const RowsLaunch& l, hipStream_t s) {
+  if (l.waves == 1 && l.per_lane == 8) launch_elem_kw<XT, SOFTMAX, 8, 1>(a, l, s);
+  else if (l.waves == 1 && l.per_lane == 12) launch_elem_kw<XT, SOFTMAX, 12, 1>(a, l, s);
+  else if (l.waves == 1) launch_elem_kw<XT, SOFTMAX, 16, 1>(a, l, s);
+  else if (l.waves == 16) launch_elem_kw<XT, SOFTMAX, 16, 16>(a, l, s);
+  else if (l.per_lane == 8) launch_elem_kw<XT, SOFTMAX, 8, 4>(a, l, s);
+  else if (l.per_lane == 16) launch_elem_kw<XT, SOFTMAX, 16, 4>(a, l, s);
+  else launch_elem_kw<XT, SOFTMAX, 32, 4>(a, l, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -663,14 +672,15 @@ void launch_vec_k(const RowArgs& a, int64_t chunks, dim3 grid, dim3 block, hipSt
 template <bool SOFTMAX>
 hipError_t launch_rows(const RowArgs& a, hipStream_t s) {
   if (a.n_rowtasks == 0) return hipSuccess;
+  const RowsLaunch l = rows_launch(a, SOFTMAX);
   const dim3 grid((uint32_t)a.n_rowtasks), block(kThreads);
-  if (a.vec) {
+  if (l.path == RowsLaunch::kVec) {
     const int64_t chunks = (int64_t)a.row_len * (a.dt_x == EA_BF16 ? 2 : 4) / 16;
     if (a.dt_x == EA_BF16) launch_vec_k<uint16_t, SOFTMAX>(a, chunks, grid, block, s);
     else launch_vec_k<float, SOFTMAX>(a, chunks, grid, block, s);
-  } else if (a.max_seg <= kMaxSeg && a.row_len <= kMaxElems) {
-    if (a.dt_x == EA_BF16) launch_elem<uint16_t, SOFTMAX>(a, s);
-    else launch_elem<float, SOFTMAX>(a, s);
+  } else if (l.path == RowsLaunch::kElem) {
+    if (a.dt_x == EA_BF16) launch_elem<uint16_t, SOFTMAX>(a, l, s);
+    else launch_elem<float, SOFTMAX>(a, l, s);
   } else {
     hipLaunchKernelGGL((rows_scalar_kernel<SOFTMAX>), grid, block, 0, s, a);
   }
@@ -678,6 +688,39 @@ hipError_t launch_rows(const RowArgs& a, hipStream_t s) {
 }
 
 }  // namespace
+
+RowsLaunch rows_launch(const RowArgs& a, bool softmax) {
+  RowsLaunch l;
+  l.grid = a.n_rowtasks;
+  l.threads = kThreads;
+  if (a.vec) {
+    l.path = RowsLaunch::kVec;
+    return l;
+  }
+  const int L = a.row_len;
+  const bool many = a.n_rowtasks > 4096 / kRowsPerTask;
+  if (a.max_seg > kMaxSeg || L > kMaxElems) return l;
+  if (!softmax && (L <= 384 || (many && a.dt_x == EA_BF16 && L > 1024 && L <= 1500))) return l;
+  if (L <= 512 || (many && L <= 1024)) {
+    l.waves = 1;
+    l.per_lane = L <= 512 ? 8 : L <= 768 ? 12 : 16;
+  } else if (L <= 8192) {
+    l.waves = 4;
+    l.per_lane = L <= 2048 ? 8 : L <= 4096 ? 16 : 32;
+  } else {
+    l.waves = 16;
+    l.per_lane = 16;
+  }
+  if (l.waves > 1) {  // one row per workgroup
+    const int64_t grid = (int64_t)a.n_rowtasks * kRowsPerTask;
+    const int32_t threads = 64 * l.waves;
+    if (grid * threads >= int64_t(1) << 32) return l;  // more than a launch holds: the scalar path
+    l.grid = grid;
+    l.threads = threads;
+  }
+  l.path = RowsLaunch::kElem;
+  return l;
+}
 
 hipError_t launch_rmsnorm(const RowArgs& a, hipStream_t s) { return launch_rows<false>(a, s); }
 hipError_t launch_softmax(const RowArgs& a, hipStream_t s) { return launch_rows<true>(a, s); }

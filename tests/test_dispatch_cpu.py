@@ -120,3 +120,38 @@ def test_contraction_tiles_read_along_k(i, j, k, tile):
 ])
 def test_large_f32_products(spec, ext, block, kind):
     assert _product(spec, ext, block, "f32")["kind"] == kind
+
+
+def _rows(op, rows, n, dtype):
+    if op == "rmsnorm":
+        return describe("tc,c->tc", ea.OP_RMSNORM, ea.AGG_SUM,
+                        [((rows, n), dtype, [[0, rows], [0, n]]), ((n,), dtype, [[0, n]]),
+                         ((rows, n), dtype, [[0, rows], [0, n]])], eps=1e-6)
+    part = [[0, rows], [0, n]]
+    return describe("qk->qk", ea.OP_SOFTMAX, ea.AGG_LSE, [((rows, n), dtype, part)] * 2)
+
+
+@pytest.mark.parametrize("op,rows,n,dtype,path,waves,per_lane", [
+    ("rmsnorm", 262144, 33, "bf16", "scalar", None, None), ("rmsnorm", 64, 383, "f32", "scalar", None, None),
+    ("rmsnorm", 32768, 385, "bf16", "elem", 1, 8), ("rmsnorm", 32768, 515, "bf16", "elem", 1, 12),
+    ("rmsnorm", 32768, 1023, "f32", "elem", 1, 16), ("rmsnorm", 1024, 515, "bf16", "elem", 4, 8),
+    ("rmsnorm", 32768, 1031, "bf16", "scalar", None, None), ("rmsnorm", 32768, 1031, "f32", "elem", 4, 8),
+    ("rmsnorm", 1024, 1031, "bf16", "elem", 4, 8), ("rmsnorm", 32768, 1501, "bf16", "elem", 4, 8),
+    ("softmax", 262144, 33, "bf16", "elem", 1, 8), ("softmax", 32768, 700, "bf16", "elem", 1, 12),
+    ("softmax", 4096, 700, "bf16", "elem", 4, 8), ("softmax", 32768, 1030, "bf16", "elem", 4, 8),
+    ("softmax", 100, 8193, "f32", "elem", 16, 16), ("softmax", 100, 16385, "f32", "scalar", None, None),
+    ("rmsnorm", 32768, 1024, "bf16", "vec", None, None),
+])
+def test_row_paths(op, rows, n, dtype, path, waves, per_lane):
+    d = _rows(op, rows, n, dtype)
+    assert (d["kind"], d["path"]) == (op, path)
+    if path == "elem":
+        assert (d["waves"], d["per_lane"]) == (waves, per_lane)
+
+
+@pytest.mark.parametrize("rows,n", [(17_000_000, 2051), (17_000_000, 515), (5_000_000, 9001)])
+def test_row_launches_hold_every_row(rows, n):
+    # rows of a workgroup or of sixteen wavefronts each: more threads than a
+    # launch holds take the scalar path, four rows per workgroup
+    d = _rows("rmsnorm", rows, n, "f32")
+    assert d["work"] * d["threads"] < 1 << 32

@@ -95,3 +95,20 @@ def test_softmax_nan_scores_stay_nan(n, dtype):
                 np.testing.assert_array_equal(np.isnan(out), np.isnan(vis))
                 assert not out[~np.isnan(vis)].any()
         assert np.isfinite(got[3]).all() and abs(got[3].sum() - 1) < 0.05
+
+
+@pytest.mark.parametrize("n", [513, 767, 769, 1023, 1025])  # one wavefront per row, 12 and 16 elements a lane; scalar
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_many_rows(n, dtype):
+    rows = 4101  # more than 4096, the last row task of one row
+    x, w = synth.normal((rows, n), 3, dtype=dtype), synth.uniform((n,), 4, 0.5, 1.5, dtype=dtype)
+    part = [[0, rows], [0, n // 2 - 1, n]]
+    X, W = upload(x, dtype, part), upload(w, dtype, part[1:])
+    Y, P = empty((rows, n), dtype, part), empty((rows, n), dtype, part)
+    ea.joinagg("tc,c->tc", ea.OP_RMSNORM, ea.AGG_SUM, [X, W], Y, eps=1e-6)
+    ea.joinagg("qk->qk", ea.OP_SOFTMAX, ea.AGG_LSE, [X], P)
+    x64 = synth.to_f64(x, dtype)
+    tol = 1e-5 if dtype == "f32" else 1e-3
+    assert_close(values(Y), expected(oracle.rmsnorm(x64, synth.to_f64(w, dtype), 1e-6), dtype), rel_fro=tol, what="rmsnorm")
+    e = np.exp(x64 - x64.max(1, keepdims=True))
+    assert_close(values(P), expected(e / e.sum(1, keepdims=True), dtype), rel_fro=tol, what="softmax")
