@@ -378,24 +378,39 @@ void key_rel(std::ostringstream& k, const ea_relation* r) {
 }
 
 // Layout ids: equal for relations of equal dtype and partition, never reused.
-// The table of known layouts is dropped when it is full; equal layouts on
-// either side of that have different ids, which costs the calls that use both
-// a full validation, no more.
-constexpr size_t kMaxLayouts = 65536;
+// The table of known layouts is dropped when it is full and with the plans;
+// equal layouts on either side of that, and those of split lists too long to
+// keep, have different ids, which costs the calls that use them a full
+// validation, no more.
+constexpr size_t kMaxLayouts = 65536, kMaxLayoutBytes = size_t(64) << 20, kMaxLayoutKey = size_t(1) << 20;
+struct Layouts {
+  std::mutex mu;
+  std::unordered_map<std::string, uint64_t> ids;
+  size_t bytes = 0;  // of the keys
+  uint64_t last = 0;
+  void drop() {
+    ids.clear();
+    bytes = 0;
+  }
+};
+Layouts& layouts() {
+  static auto* l = new Layouts();  // intentionally leaked at exit
+  return *l;
+}
 uint64_t layout_id(const ea_relation* r) {
-  static std::mutex mu;
-  static auto* ids = new std::unordered_map<std::string, uint64_t>();  // intentionally leaked at exit
-  static uint64_t last = 0;
   std::string k;
   k.append(reinterpret_cast<const char*>(&r->dtype), sizeof(r->dtype));
   for (int d = 0; d < r->rank; ++d)  // every list starts at 0 and increases: the concatenation is unambiguous
     k.append(reinterpret_cast<const char*>(r->splits[d].data()), r->splits[d].size() * sizeof(int64_t));
-  std::lock_guard<std::mutex> lk(mu);
-  auto it = ids->find(k);
-  if (it != ids->end()) return it->second;
-  if (ids->size() >= kMaxLayouts) ids->clear();
-  ids->emplace(std::move(k), ++last);
-  return last;
+  Layouts& l = layouts();
+  std::lock_guard<std::mutex> lk(l.mu);
+  auto it = l.ids.find(k);
+  if (it != l.ids.end()) return it->second;
+  if (k.size() > kMaxLayoutKey) return ++l.last;
+  if (l.ids.size() >= kMaxLayouts || l.bytes + k.size() > kMaxLayoutBytes) l.drop();
+  l.bytes += k.size();
+  l.ids.emplace(std::move(k), ++l.last);
+  return l.last;
 }
 
 // Allocate a device buffer for a plan image and upload the image into it.
@@ -2081,15 +2096,20 @@ std::unordered_map<std::string, Call>& calls() {  // guarded by g_cache_mu
   static auto* m = new std::unordered_map<std::string, Call>();  // intentionally leaked at exit
   return *m;
 }
-constexpr size_t kMaxCalls = 65536;  // dropped when full
+constexpr size_t kMaxCalls = 65536, kMaxCallBytes = size_t(64) << 20;  // dropped when full
+size_t g_call_bytes = 0;  // of the keys
 
 // Enters a call whose plan was found in `generation`.  A cache cleared since then
 // has freed the plan: the call is not entered.
-bool remember_call(std::string key, const Call& c, uint64_t generation) {
+bool remember_call(const std::string& key, const Call& c, uint64_t generation) {
   std::lock_guard<std::mutex> lk(g_cache_mu);
   if (generation != g_generation) return false;
-  if (calls().size() >= kMaxCalls) calls().clear();
-  calls().emplace(std::move(key), c);
+  if (calls().size() >= kMaxCalls || g_call_bytes + key.size() > kMaxCallBytes) {
+    calls().clear();
+    g_call_bytes = 0;
+  }
+  g_call_bytes += key.size();
+  if (!calls().emplace(key, c).second) g_call_bytes -= key.size();
   return true;
 }
 bool known_call(const std::string& key, Call* c) {
@@ -2152,7 +2172,7 @@ int find_call(const char* spec, int32_t join_op, int32_t agg_op, int32_t n_in, c
   int e = prepare(spec, join_op, agg_op, n_in, in, out, params, need_data, build, s, &sp, &oi, &plan, &generation);
   if (e) return e;
   *call = Call{plan, oi.causal, oi.q_dim, oi.k_dim};
-  if (!key.empty()) remember_call(std::move(key), *call, generation);
+  if (!key.empty()) remember_call(key, *call, generation);
   return EA_OK;
 }
 
@@ -2780,7 +2800,7 @@ int get_repartition_plan(const ea_relation* src, const ea_relation* dst, bool bu
     }
   }
   call.plan = plan;
-  remember_call(std::move(short_key), call, generation);
+  remember_call(short_key, call, generation);
   *out = plan;
   return EA_OK;
 }
@@ -2874,6 +2894,11 @@ uint64_t ea_internal_generation(void) {
   return g_generation;
 }
 int ea_internal_remember(const char* key, uint64_t generation) { return remember_call(key, Call(), generation); }
+int64_t ea_internal_table_bytes(void) {
+  std::lock_guard<std::mutex> lk(g_cache_mu);
+  std::lock_guard<std::mutex> ll(layouts().mu);
+  return (int64_t)(g_call_bytes + layouts().bytes);
+}
 
 int64_t ea_plan_cache_size(void) {
   std::lock_guard<std::mutex> lk(g_cache_mu);
@@ -2884,6 +2909,11 @@ int ea_plan_cache_clear(void) {
   std::lock_guard<std::mutex> lk(g_cache_mu);
   ++g_generation;
   calls().clear();  // they point into the plans
+  g_call_bytes = 0;
+  {
+    std::lock_guard<std::mutex> ll(layouts().mu);
+    layouts().drop();
+  }
   cache().clear();
   return ok();
 }

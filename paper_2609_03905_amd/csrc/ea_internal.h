@@ -514,3 +514,5 @@ extern "C" int ea_internal_describe(const char* spec, int32_t join_op, int32_t a
 // with no plan): for the tests of that table.
 extern "C" uint64_t ea_internal_generation(void);
 extern "C" int ea_internal_remember(const char* key, uint64_t generation);
+// Bytes of the keys that the tables of layouts and of recognised calls hold.
+extern "C" int64_t ea_internal_table_bytes(void);

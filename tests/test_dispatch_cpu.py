@@ -155,3 +155,23 @@ def test_row_launches_hold_every_row(rows, n):
     # launch holds take the scalar path, four rows per workgroup
     d = _rows("rmsnorm", rows, n, "f32")
     assert d["work"] * d["threads"] < 1 << 32
+
+
+def test_tables_of_layouts_and_calls_are_bounded_and_given_back():
+    L = ea.lib()
+    L.ea_internal_table_bytes.restype = ctypes.c_int64
+    n, bound = 100_000, 64 << 20
+    nb, splits, h = (ctypes.c_int32 * 1)(n), (ctypes.c_int64 * (n + 1))(*range(n + 1)), ctypes.c_void_p()
+    ids = 0
+    for i in range(200):  # 160 MB of split points in all
+        splits[n] = n + i
+        assert L.ea_relation_create(1, (ctypes.c_int64 * 1)(n + i), 0, nb, splits, None, 0, ctypes.byref(h)) == 0
+        L.ea_relation_destroy(h)
+        ids = max(ids, L.ea_internal_table_bytes())
+    assert 8 * n < ids <= 2 * bound
+    L.ea_internal_generation.restype = ctypes.c_uint64
+    for i in range(2000):  # 200 MB of call keys
+        assert L.ea_internal_remember(b"%099999d" % i, ctypes.c_uint64(L.ea_internal_generation())) == 1
+    assert L.ea_internal_table_bytes() <= 2 * bound
+    ea.plan_cache_clear()
+    assert L.ea_internal_table_bytes() == 0
