@@ -282,6 +282,14 @@ int analyze_join(const Spec& sp, const ea_relation* const* ops, const std::strin
 // ---------------------------------------------------------------------------
 struct Image {
   std::vector<uint8_t> bytes;
+  size_t tail = 0;  // device memory after the image, written by plan-time kernels (reserve)
+  size_t size() const { return bytes.size() + tail; }
+  // Device memory of n bytes without initial value; nothing is put after it.
+  size_t reserve(size_t n) {
+    const size_t o = (size_t)align256((int64_t)bytes.size());
+    tail = o + n - bytes.size();
+    return o;
+  }
   size_t put(const void* p, size_t n) {
     size_t o = (size_t)align256((int64_t)bytes.size());
     bytes.resize(o + std::max<size_t>(n, 1), 0);
@@ -415,13 +423,13 @@ uint64_t layout_id(const ea_relation* r) {
 
 // Allocate a device buffer for a plan image and upload the image into it.
 int upload_image(const Image& img, char** mem, hipStream_t s) {
-  EA_HIP_TRY(hipMalloc((void**)mem, std::max<size_t>(img.bytes.size(), 256)));
+  EA_HIP_TRY(hipMalloc((void**)mem, std::max<size_t>(img.size(), 256)));
   EA_HIP_TRY(hipMemcpyAsync(*mem, img.bytes.data(), img.bytes.size(), hipMemcpyHostToDevice, s));
   return EA_OK;
 }
 
 int plan_upload(Plan* p, const Image& img, hipStream_t s) {
-  p->dbytes = img.bytes.size();
+  p->dbytes = img.size();
   EA_HIP_TRY(hipGetDevice(&p->device));
   return upload_image(img, &p->dmem, s);
 }
@@ -1415,7 +1423,7 @@ int build_contract(const ea_relation* const* ops, const ContractDims& d, int64_t
   }
   ex->work = img->put_vec(work);
   ex->n_work = (int64_t)work.size();
-  ex->meta = img->put_zero((size_t)tuple_cap * sizeof(ConMeta));
+  ex->meta = img->reserve((size_t)tuple_cap * sizeof(ConMeta));
   return EA_OK;
 }
 
@@ -1575,7 +1583,7 @@ int build_reduce(const ea_relation* const* ops, int n_in, int32_t join_op, int32
   }
   ex->work = img->put_vec(work);
   ex->n_work = (int64_t)work.size();
-  ex->meta = img->put_zero((size_t)tuple_cap * sizeof(RedMeta));
+  ex->meta = img->reserve((size_t)tuple_cap * sizeof(RedMeta));
   return EA_OK;
 }
 
@@ -1862,7 +1870,7 @@ int plan_image(const Spec& sp, int32_t join_op, int32_t agg_op, const ea_relatio
       if (p->gemm_direct) {
         ex->work = img->put_vec(dl.units);
         ex->n_work = (int64_t)dl.units.size();
-        ex->meta = img->put_zero((size_t)p->tuple_cap * sizeof(GemmTupleMeta));
+        ex->meta = img->reserve((size_t)p->tuple_cap * sizeof(GemmTupleMeta));
         slots = dl.slots;
         p->ws_counters = dl.counters;
         p->gemm_balanced = dl.balanced;
@@ -2882,7 +2890,8 @@ int ea_internal_describe(const char* spec, int32_t join_op, int32_t agg_op, int3
     case K_ATTENTION: t << "kind=attention"; break;
     default: t << "kind=other";
   }
-  t << " work=" << p.n_work << " threads=" << threads << " table_bytes=" << img.bytes.size() << " ws=" << p.ws_bytes();
+  t << " work=" << p.n_work << " threads=" << threads << " table_bytes=" << img.size() << " host_bytes=" << img.bytes.size()
+    << " ws=" << p.ws_bytes();
   if (!text || cap < (int64_t)t.str().size() + 1) return fail(EA_ERR_CAPACITY, "describe: text buffer too small");
   memcpy(text, t.str().c_str(), t.str().size() + 1);
   return ok();

@@ -175,3 +175,17 @@ def test_tables_of_layouts_and_calls_are_bounded_and_given_back():
     assert L.ea_internal_table_bytes() <= 2 * bound
     ea.plan_cache_clear()
     assert L.ea_internal_table_bytes() == 0
+
+
+@pytest.mark.parametrize("spec,ext,block,dtype", [
+    ("ij,jk->ik", dict(i=1024, j=1024, k=1024), 16, "f32"), ("ij,jk->ik", dict(i=2048, j=2048, k=2048), 16, "bf16"),
+])
+def test_tuple_records_are_made_on_the_device(spec, ext, block, dtype):
+    # a record of 64 or 72 bytes per tuple beside the join's own 8 or 12: in
+    # device memory alone, not in the image that the host builds and uploads
+    d = _product(spec, ext, block, dtype, agg=SUM)
+    tuples = 1
+    for n in ext.values():
+        tuples *= n // block
+    assert d["kind"] in ("contract", "gemm")
+    assert d["table_bytes"] >= 64 * tuples and d["host_bytes"] < 40 * tuples
