@@ -2,13 +2,15 @@
 be part of what it is recognised by, and what is not (data pointers) must be
 looked at every time."""
 import ctypes
+import threading
 
 import numpy as np
 import pytest
 import torch
 
+import oracle
 import synth
-from helpers import upload
+from helpers import assert_close, empty, expected, upload, values
 from paper_2609_03905_amd import ea
 
 pytestmark = pytest.mark.gpu
@@ -27,8 +29,116 @@ def test_parameters_layouts_and_data_are_all_seen():
     a = _rms(x, w, 1e-6, [0, 64])
     assert _rms(x, w, 10.0, [0, 64]) != a          # another eps, same layouts
     assert _rms(x, w, 1e-6, [0, 32, 64]) != a      # another partition, same shape
-    assert _rms(2.0 * x, w, 1e-6, [0, 64]) is not None
+    y = np.ascontiguousarray(x[:, ::-1])           # other data
+    got = np.frombuffer(_rms(y, w, 1e-6, [0, 64]), np.float32).reshape(8, 64)
+    ref = oracle.rmsnorm(y.astype(np.float64), w.astype(np.float64), 1e-6)
+    assert np.linalg.norm(got - ref) < 1e-6 * np.linalg.norm(ref)
     assert _rms(x, w, 1e-6, [0, 64]) == a
+
+
+def test_data_pointers_are_read_on_every_call():
+    # inputs, residual and output moved to other buffers between two recognised
+    # calls: the second result goes to the new output, the first stays
+    p = [[0, 64], [0, 64]]
+    xs = [synth.integers((64, 64), i, -3, 3, "f32") for i in range(6)]
+    run = lambda: ea.joinagg("ij,jk->ik", ea.JOIN_MUL, ea.AGG_SUM, [A, B], C, residual=R)
+    A, B, R = (upload(x, "f32", p) for x in xs[:3])
+    C = empty((64, 64), "f32", p)
+    run()
+    run()
+    first, old = values(C), C.data
+    np.testing.assert_array_equal(first, xs[0].astype(np.float64) @ xs[1] + xs[2])
+    moved = [upload(x, "f32", p) for x in xs[3:]] + [empty((64, 64), "f32", p)]
+    keep = []  # the old buffers, so that their addresses are not handed out again
+    for rel, new in zip((A, B, R, C), moved):
+        assert ea.lib().ea_relation_set_data(rel.handle, new.data.data_ptr(), new.data.numel()) == ea.OK
+        keep.append(rel.data)
+        rel.data = new.data
+    run()
+    np.testing.assert_array_equal(values(C), xs[3].astype(np.float64) @ xs[4] + xs[5])
+    C.data = old
+    np.testing.assert_array_equal(values(C), first)
+
+
+def test_attention_parameters_separate_calls():
+    # the same relations under another scale, mask, list of sequences or
+    # grouping: each call against its own, and again in the other order
+    S, part = 384, [[0, 1], [0, 1, 2], [0, 128, 256, 384], [0, 128]]
+    q, k, v = (synth.normal((1, 2, S, 128), i, dtype="bf16") for i in (1, 2, 3))
+    Q, K, V = (upload(x, "bf16", part) for x in (q, k, v))
+    calls = [dict(scale=0.08), dict(scale=0.02), dict(scale=0.08, causal=True), dict(scale=0.08, seq_ends=[128, 384]),
+             dict(scale=0.08, seq_ends=[256, 384]), dict(scale=0.08, causal=True, seq_ends=[256, 384])]
+    first = {}
+    for order in (range(6), reversed(range(6))):
+        for i in order:
+            c = calls[i]
+            O = empty((1, 2, S, 128), "bf16", part)
+            ea.joinagg("bhqd,bhkd,bhkd->bhqd", ea.OP_ATTENTION, ea.AGG_LSE, [Q, K, V], O, **c)
+            got, ends, lo = values(O), c.get("seq_ends", [S]), 0
+            for hi in ends:
+                ref = oracle.attention(*(synth.to_f64(x[:, :, lo:hi], "bf16") for x in (q, k, v)), c.get("causal", False),
+                                       c["scale"])
+                assert_close(got[:, :, lo:hi], expected(ref, "bf16"), what=str(c))
+                lo = hi
+            assert np.array_equal(first.setdefault(i, got), got)
+    # two query heads over one key/value head: other relations for K and V, one
+    # grouping parameter apart from a call that is refused
+    g = [[0, 1], [0, 1], part[2], part[3]]
+    K1, V1 = upload(k[:, :1], "bf16", g), upload(v[:, :1], "bf16", g)
+    O = empty((1, 2, S, 128), "bf16", part)
+    run = lambda **kw: ea.joinagg("bhqd,bgkd,bgkd->bhqd", ea.OP_ATTENTION, ea.AGG_LSE, [Q, K1, V1], O, scale=0.08, **kw)
+    for _ in range(2):
+        run(gqa_group=2)
+        with pytest.raises(ea.EAError):
+            run()
+    rep = [synth.to_f64(np.repeat(x[:, :1], 2, 1), "bf16") for x in (k, v)]
+    assert_close(values(O), expected(oracle.attention(synth.to_f64(q, "bf16"), *rep, False, 0.08), "bf16"), what="gqa")
+
+
+def test_residual_layouts_separate_calls():
+    # with and without a residual, and with one of another partition (refused)
+    p = [[0, 64], [0, 96]]
+    a, r = synth.integers((64, 96), 1, -3, 3, "f32"), synth.integers((64, 96), 2, -3, 3, "f32")
+    A, R, other = upload(a, "f32", p), upload(r, "f32", p), upload(r, "f32", [[0, 32, 64], [0, 96]])
+    C = empty((64, 96), "f32", p)
+    run = lambda res: ea.joinagg("ij->ij", ea.JOIN_MUL, ea.AGG_NONE, [A], C, residual=res)
+    for _ in range(2):
+        run(None)
+        np.testing.assert_array_equal(values(C), a)
+        run(R)
+        np.testing.assert_array_equal(values(C), a.astype(np.float64) + r)
+        with pytest.raises(ea.EAError):
+            run(other)
+
+
+def test_two_threads_on_the_table_of_calls():
+    # both threads make calls that are new to the table and calls known to it,
+    # each on its own stream and relations
+    p = lambda n: [[0, n], [0, 64]]
+    done, errors = [], []
+
+    def work(t):
+        try:
+            s = torch.cuda.Stream()
+            with torch.cuda.stream(s):
+                for i in range(40):
+                    n = 64 + 8 * (i % 10) + (t if i % 2 else 0)  # half of the layouts are common
+                    x = synth.integers((n, 64), 100 * t + i, -3, 3, "f32")
+                    X, Y = upload(x, "f32", p(n)), ea.Relation((n,), "f32", [[0, n]])
+                    ea.joinagg("ij->i", ea.JOIN_MUL, ea.AGG_SUM, [X], Y)
+                    s.synchronize()
+                    got = Y.bytes().view(torch.float32).cpu().numpy()
+                    np.testing.assert_array_equal(got, x.sum(1))
+            done.append(t)
+        except BaseException as e:  # noqa: BLE001  (reported below)
+            errors.append(e)
+
+    threads = [threading.Thread(target=work, args=(t,)) for t in (0, 1)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join(60)
+    assert not errors and sorted(done) == [0, 1], errors
 
 
 def test_invalid_calls_stay_invalid_after_valid_ones():
