@@ -56,8 +56,8 @@
  * Errors.  Every call returns EA_OK (0) or a negative EA_ERR_* code and sets a
  * thread-local message (ea_last_error).  No exception crosses the ABI.
  * Argument, spec, partition and join validation runs on the host before any
- * HIP call, so it works without a GPU.  Kernel faults surface as EA_ERR_HIP at
- * the call that observes them.
+ * HIP call but the query of the current device, so it works without a GPU.
+ * Kernel faults surface as EA_ERR_HIP at the call that observes them.
  */
 #ifndef EA_H
 #define EA_H
@@ -202,8 +202,10 @@ int ea_relation_block(const ea_relation* rel, int64_t b, int64_t* lo, int64_t* h
    split points in each (EA_ERR_JOIN otherwise: repartition first); the
    output's partition on each letter must equal the inputs' (EA_ERR_JOIN).
    Tuples are grouped by output key; inside a group they are combined by
-   agg_op in ascending order of the contracted letters' blocks, so results
-   are deterministic (no atomics in the combine).
+   agg_op in an order that the plan fixes (ascending along the contracted
+   letters' blocks, in one or several runs whose partial results are then
+   combined in order), so results are deterministic (no atomics in the
+   combine).
 
    join_op EA_JOIN_MUL / EA_JOIN_ADD, agg_op NONE / SUM / MAX: out[o] =
      AGG over contracted letter values of JOIN(in_1[..], ..., in_n[..]),

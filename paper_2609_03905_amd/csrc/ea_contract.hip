@@ -2,11 +2,14 @@
 //
 // Section 3.2, Example "Matrix multiply, decomposed": every tuple of an output
 // key multiplies one block of A by one block of B and the products are summed
-// (aggregation +).  This kernel takes every such join-agg whose letters fall
-// into one contracted letter (in both inputs), at most one row letter (A and
-// output), at most one column letter (B and output) and any batch letters (all
-// three), whatever their order in the operands: "ij,jk->ik", "ij,kj->ik",
-// "hqd,hkd->hqk", "bij,bjk->bik", "tj,j->t", ...  f32, bf16 and f16 operands
+// (aggregation +).  These kernels take such join-aggs whose letters fall into
+// one contracted letter (in both inputs), at most one row letter (A and
+// output), at most one column letter (B and output), one of the two at least,
+// and any batch letters (all three), whatever their order in the operands:
+// "ij,jk->ik", "ij,kj->ik", "hqd,hkd->hqk", "bij,bjk->bik", "tj,j->t", ...  Left
+// to others: blocks of 2 GiB and more (32-bit byte offsets), and products of
+// which a tile holds few outputs, where reduction_faster in the host code
+// estimates so.  f32, bf16 and f16 operands
 // are widened to fp32 (exact) and multiplied by v_mfma_f32_*_f32, so products
 // and sums keep fp32 precision; 16-bit products "ab,bc->ac" with 8-aligned
 // blocks take the 16-bit matrix-core kernel instead.

@@ -26,9 +26,9 @@
 //     occupancy (64 B per clock and CU against the 58 it delivers), by one
 //     wave's step time with one workgroup per CU.  GPU time, bf16 in
 //     512-blocks, 256-row plan -> 128-row plan:
-//       64 x 4096 x 4096     35 -> 17 us     1024 x 1024 x 1024  18.5 -> 12 us
-//       1001 x 2744 x 2008   36 -> 27 us     2048 x 2048 x 2048  32 -> 24 us
-//       1024 x 4096 x 4096   59 -> 43 us     4096 x 4096 x 4096  114 | 154 us
+//       64 x 4096 x 4096     34 -> 17 us     1024 x 1024 x 1024  18 -> 11 us
+//       1001 x 2744 x 2008   32 -> 26 us     2048 x 2048 x 2048  32 -> 25 us
+//       1024 x 4096 x 4096   52 -> 43 us     4096 x 4096 x 4096  111 | 154 us
 //
 // Two K pipelines share the tile layout and the epilogue:
 //   * gemm_dl_kernel: operands go straight from global memory into LDS
@@ -40,8 +40,8 @@
 //     double-buffered with padded rows; a right operand stored [k][n] is
 //     transposed in registers before the LDS write.  For what the direct loads
 //     do not take: more tuples per output block than their LDS table holds, or
-//     operand blocks of 4 GiB and more (1001 x 2744 x 2008, f16: 52 us here,
-//     36 us with direct loads into the same tiles).
+//     operand blocks of 4 GiB and more (1001 x 2744 x 2008, bf16: 51 us here,
+//     32 us with direct loads into the same tiles).
 //
 // Epilogue: the tile is staged through LDS so that stores (and the residual
 // loads) are 16-byte row chunks; the residual is added in fp32 before the one

@@ -8,11 +8,12 @@
 // the slow, general path; two-operand products with a contracted letter take
 // the matrix-core kernels, and reduce_kernel below takes the einsums of one or
 // two inputs of one dtype with at most one contracted letter and four output
-// letters (row and column reductions, elementwise joins, broadcasts,
-// transposes): element addresses from strides resolved when the plan is built,
+// letters (row and column reductions, sums of products that fill no tile,
+// elementwise joins, broadcasts, transposes; not those over blocks of a few
+// elements): element addresses from strides resolved when the plan is built,
 // and the contracted letter shared between threads:
 //   * lanes along the contracted letter where it is the input's contiguous one
-//     ("ij->i"): a wavefront, or four, per output element;
+//     ("ij->i") and long, or the outputs few: a wavefront, or four, per output;
 //   * lanes along the output otherwise ("ij->j", "ij,ij->ij"): one, four or
 //     sixteen wavefronts per 64 output elements.
 // Both are bound by memory for large inputs and by latency (launch, three
