@@ -1282,7 +1282,8 @@ GemmDlPlan gemm_units_dl(const ea_relation* a, const ea_relation* c, int tn, int
   //   SwiGLU 1792 x 8192 x 2752   1.00 | 0.75   211.5 | 158.9 us
   //          1536 x 8192 x 3072   0.69 | 0.31   154.9 | 147.5
   //          1024 x 8192 x 5504   0.69 | 0.51   181.8 | 174.2
-  //          2048 x 8192 x 2752   0.38 | 0.33   168.9 | 168.6 (kept in block order)
+  //          2048 x 8192 x 2752   0.38 | 0.33   168.9 | 168.6 (kept in block order;
+  //            with new inputs on every pass 179.3 | 176.9, on another card 179.7 | 180.2)
   //          2048 x 8192 x 2304   0.35 | 0.33   150.0 | 148.9 (kept in block order)
   //   plain  2560 x 8192 x 3584   1.00 | 0.50   193.0 | 147.1
   //          2560 x 4096 x 3584   1.00 | 0.50   112.9 |  86.8
