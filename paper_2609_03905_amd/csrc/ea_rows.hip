@@ -454,8 +454,11 @@ __global__ __launch_bounds__(kThreads * WPR) void rows_vec_kernel(RowArgs a) {
 // GPU at four wavefronts each (4096), rows of up to 1024 elements take one
 // wavefront too: there the table and barriers of a row are what counts.  And
 // RMSNorm keeps the scalar path where its second read comes from the cache and
-// costs less than the table: up to 384 elements, and with many bf16 rows between
-// 1024 and 1500.  us, scalar | one wavefront | four:
+// costs less than the table: up to 384 elements in one segment (it walks the
+// segments one after the other: 65536 x 60 in 60 segments 683 us there, 50
+// here), and with many bf16 rows between 1024 and 1500 in up to two or three
+// (32768 x 1031 in three 82 | 91 us, x 1401 in three 110 | 107).  us, scalar |
+// one wavefront | four:
 //   RMSNorm 32768 x 515 bf16    41 | 40 | 63    262144 x 33 bf16    75 | 83
 //           32768 x 769 bf16    57 | 54 | 76    32768 x 300 bf16  25.5 | 26.5
 //           32768 x 1031 bf16   73 | 86 | 89    32768 x 500 bf16  38.3 | 37.1
@@ -700,7 +703,9 @@ RowsLaunch rows_launch(const RowArgs& a, bool softmax) {
   const int L = a.row_len;
   const bool many = a.n_rowtasks > 4096 / kRowsPerTask;
   if (a.max_seg > kMaxSeg || L > kMaxElems) return l;
-  if (!softmax && (L <= 384 || (many && a.dt_x == EA_BF16 && L > 1024 && L <= 1500))) return l;
+  if (!softmax && ((L <= 384 && a.max_seg == 1) ||
+                   (many && a.dt_x == EA_BF16 && L > 1024 && L <= 1500 && a.max_seg * L <= 3600)))
+    return l;
   if (L <= 512 || (many && L <= 1024)) {
     l.waves = 1;
     l.per_lane = L <= 512 ? 8 : L <= 768 ? 12 : 16;

@@ -122,12 +122,11 @@ def test_large_f32_products(spec, ext, block, kind):
     assert _product(spec, ext, block, "f32")["kind"] == kind
 
 
-def _rows(op, rows, n, dtype):
+def _rows(op, rows, n, dtype, nseg=1):
+    part = [[0, rows], synth.splits(n, -(-n // nseg))]
     if op == "rmsnorm":
         return describe("tc,c->tc", ea.OP_RMSNORM, ea.AGG_SUM,
-                        [((rows, n), dtype, [[0, rows], [0, n]]), ((n,), dtype, [[0, n]]),
-                         ((rows, n), dtype, [[0, rows], [0, n]])], eps=1e-6)
-    part = [[0, rows], [0, n]]
+                        [((rows, n), dtype, part), ((n,), dtype, part[1:]), ((rows, n), dtype, part)], eps=1e-6)
     return describe("qk->qk", ea.OP_SOFTMAX, ea.AGG_LSE, [((rows, n), dtype, part)] * 2)
 
 
@@ -147,6 +146,15 @@ def test_row_paths(op, rows, n, dtype, path, waves, per_lane):
     assert (d["kind"], d["path"]) == (op, path)
     if path == "elem":
         assert (d["waves"], d["per_lane"]) == (waves, per_lane)
+
+
+@pytest.mark.parametrize("rows,n,nseg,path", [
+    (65536, 60, 60, "elem"), (65536, 33, 2, "elem"), (65536, 33, 1, "scalar"), (32768, 1201, 2, "scalar"), (32768, 1031, 3, "scalar"),
+    (32768, 1031, 5, "elem"), (32768, 1401, 3, "elem"),
+])
+def test_rmsnorm_in_segments(rows, n, nseg, path):
+    # the scalar path walks the segments one after the other
+    assert _rows("rmsnorm", rows, n, "bf16", nseg)["path"] == path
 
 
 @pytest.mark.parametrize("rows,n", [(17_000_000, 2051), (17_000_000, 515), (5_000_000, 9001)])
