@@ -737,11 +737,18 @@ ContractChoice contract_choice(const ea_relation* const* ops, const ContractDims
 //   2^20 x 16 by a vector          103 |  34 (107 |  54)    85
 //   32768 of 4 x 256 x 1            80 | 122 (166 | 104)   435
 //   20000 of 16 x 16 x 16           26 |  36 ( 38 | 249)   470
+//   16384 of 4 x 16 x 4, one a block 17 |  29 ( 31 |  32)  1584
 //   4096 x 4096 by a vector       13.4 |  15 ( 17 |  54)  3618
 bool reduction_faster(const ea_relation* const* ops, const ContractDims& d) {
-  double terms = (double)ops[d.a_op]->shape[d.ak];
-  for (int x = 0; x < ops[2]->rank; ++x) terms *= (double)ops[2]->shape[x];
-  return 3.5 + 3.0e-6 * terms < 0.6 * contract_choice(ops, d).us;
+  const ea_relation *A = ops[d.a_op], *B = ops[1 - d.a_op], *C = ops[2];
+  const double K = (double)A->shape[d.ak];
+  double terms = K;
+  for (int x = 0; x < C->rank; ++x) terms *= (double)C->shape[x];
+  // a workgroup per output block at least, and with lanes along the output a
+  // sixteenth of the contracted letter one term after the other
+  const bool along = d.ak == A->rank - 1 && d.bk == B->rank - 1;
+  const double us = 3.5 + 3.0e-6 * terms + 1.0e-3 * (double)C->nblocks + (along ? 0.0 : 4.0e-3 * K);
+  return us < 0.62 * contract_choice(ops, d).us;
 }
 
 bool is_float_dtype(int32_t dt) { return dt == EA_F32 || dt == EA_BF16 || dt == EA_F16; }
@@ -1541,15 +1548,18 @@ int build_reduce(const ea_relation* const* ops, int n_in, int32_t join_op, int32
   // Lanes along a contiguous contracted letter (rows), a wavefront per output,
   // or four where one each leaves CUs idle; else along the output, and as many
   // wavefronts per 64 elements as it takes to have about 2000 of them, each
-  // with at least 8 terms.  A wavefront per output costs 0.4 ns an output (and
-  // 0.09 ns a tuple) whatever the length, lanes along the output 0.5 ns per 256
-  // terms: with many outputs rows win from about 200 terms on in blocks of 64
-  // or more.  us, f32, rows | lanes along the output:
+  // with at least 8 terms.  With many outputs a wavefront each costs 0.4 ns and
+  // 0.085 ns per further tuple, lanes along the output 2 ps a term in one tuple
+  // and 2.6 to 3.5 (fewer than 2^17 outputs) in several.  us, f32, rows | lanes
+  // along the output:
   //   2^20 x 64   416 | 129     2^20 x 256 in 64-blocks   627 | 693
   //   2^20 x 128  428 | 279                in 32-blocks   948 | 698
   //   2^20 x 256  427 | 564                in 4-blocks   5371 | 256
   //   2^15 x 64  15.0 | 6.2     2^15 x 512  16.4 | 31     2^12 x 64  4.7 | 4.9
-  a->rows = along && len >= 32 && (outputs <= 12288 || (len >= 200 && len >= 64 * (int64_t)a->nt));
+  //   13000 x 2048 in 63-blocks  42 | 109    65536 x 2048 in 8-blocks 1388 | 226
+  const double per_row = 0.4 + 0.085 * (a->nt - 1);  // ns
+  const double per_term = a->nt == 1 ? 0.002 : outputs < 131072 ? 0.0035 : 0.0026;
+  a->rows = along && len >= 32 && (outputs <= 12288 || per_row < per_term * (double)len);
   a->rounds = 1;
   a->threads = 256;
   if (a->rows) {

@@ -62,6 +62,7 @@ SUM, MAX, NONE = ea.AGG_SUM, ea.AGG_MAX, ea.AGG_NONE
 @pytest.mark.parametrize("i,j,jblock,rows", [
     (1 << 20, 64, 64, 0), (1 << 20, 128, 128, 0), (1 << 20, 256, 256, 1), (1 << 20, 256, 32, 0), (1 << 20, 256, 4, 0),
     (1 << 20, 256, 64, 1), (32768, 64, 64, 0), (32768, 512, 512, 1), (4096, 64, 64, 1), (4096, 2048, 8, 1), (4096, 31, 31, 0),
+    (13000, 2048, 63, 1), (100000, 512, 63, 1), (65536, 2048, 8, 0),
 ])
 def test_reduction_lanes(i, j, jblock, rows):
     # a wavefront per output or lanes along the output, whichever measured
@@ -100,6 +101,16 @@ def test_reduction_tables_and_launches_stay_small(i, j, dtype):
 ])
 def test_contraction_or_reduction(spec, ext, kind):
     assert _product(spec, ext, 1 << 30, "f32")["kind"] == kind
+
+
+@pytest.mark.parametrize("spec,ext,block,kind", [
+    ("bij,bjk->bik", dict(b=16384, i=4, j=16, k=4), dict(b=1), "contract"),  # a workgroup per block either way
+    ("bij,bjk->bik", dict(b=65536, i=4, j=16, k=4), dict(b=1024), "reduce"),
+    ("ij,i->j", dict(i=8192, j=100), dict(i=512), "contract"),                # a long serial sum per lane
+    ("ij,j->i", dict(i=1 << 20, j=16), dict(j=8), "reduce"),
+])
+def test_contraction_or_reduction_in_blocks(spec, ext, block, kind):
+    assert _product(spec, ext, block, "f32")["kind"] == kind
 
 
 @pytest.mark.parametrize("i,j,k,tile", [
